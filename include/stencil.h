@@ -572,8 +572,9 @@ stencil_status stencil_check(stencil_plan plan, void* const* fields, stencil_che
 
 /* Kernel variants of a plan (this library's kernel choices: no passage of
  * the paper; the temporally blocked ones follow the overlapped temporal
- * blocking of Section 7's related work).  Variant 0 is the
- * one-thread-per-point kernel.
+ * blocking of Section 7's related work).  Variant 0, "point", is the
+ * general kernel: one thread per point in 1D and 2D, bricks of 64 x 16 x 2 or
+ * 4 points in 3D (the fastest there on grids too small for the others).
  * 3D plans add the z-marching sweep (tile shape and z-chunk), and for the
  * radius-4 wave and the FP32 heat with the zero halo the depth-2 temporally
  * blocked sweep (two steps per launch).  2D FP32 heat plans with the zero

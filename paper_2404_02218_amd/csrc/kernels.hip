@@ -1,7 +1,7 @@
 // HIP kernels of the star-stencil sweep for gfx950 (CDNA4, 64-wide waves).
 //
-//  k_point   one thread per output point of a box: the general kernel for
-//            1D/2D plans, sub-box applies, and variant 0 of 3D plans.
+//  k_point   one thread per output point of a box of a 1D or 2D plan.
+//  k_zbrick  (zbrick.hip) 3D sub-box applies, and variant 0 of 3D plans.
 //  k_zmarch  the 3D sweep: each workgroup owns an xy tile (TX x TY) and marches
 //            a chunk of z.  Every thread keeps the 2r+1 planes of its own
 //            columns in registers (the z taps), stages the current plane with
@@ -32,25 +32,16 @@ namespace stn {
 template <int MODE, int R, typename T, int ND>
 __global__ __launch_bounds__(256) void k_point(ZView v, Coefs w, Box3 box) {
     using S = Storage<T>;
-    const int64_t total = box.n[0] * box.n[1] * box.n[2];
+    const int64_t total = box.n[1] * box.n[2];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= total) return;
     const int64_t x = box.lo[2] + i % box.n[2];
-    const int64_t y = box.lo[1] + (i / box.n[2]) % box.n[1];
-    const int64_t z = box.lo[0] + i / (box.n[2] * box.n[1]);
-    const int64_t off = v.g.origin + z * v.g.s[0] + y * v.g.s[1] + x;
+    const int64_t y = box.lo[1] + i / box.n[2];
+    const int64_t off = v.g.origin + y * v.g.s[1] + x;
     const T* U = (const T*)v.u;
     const float ctr = S::load(U + off);
     float acc = w.cd0 * ctr;
     float m[R], p[R];
-    if constexpr (ND == 3) {
-#pragma unroll
-        for (int k = 1; k <= R; k++) {
-            m[k - 1] = S::load(U + off - k * v.g.s[0]);
-            p[k - 1] = S::load(U + off + k * v.g.s[0]);
-        }
-        acc = axis_sum<R>(acc, w, m, p);
-    }
     if constexpr (ND >= 2) {
 #pragma unroll
         for (int k = 1; k <= R; k++) {
@@ -71,7 +62,7 @@ __global__ __launch_bounds__(256) void k_point(ZView v, Coefs w, Box3 box) {
         beta = S::load((const T*)v.beta + off);
     }
     if constexpr (MODE == MODE_WAVE_DAMP) {
-        const float g = (v.damp[z] + v.damp[v.g.n[0] + y]) + v.damp[v.g.n[0] + v.g.n[1] + x];
+        const float g = (v.damp[0] + v.damp[v.g.n[0] + y]) + v.damp[v.g.n[0] + v.g.n[1] + x];
         S::store((T*)v.out + off, damped_update(acc, ctr, prev, beta, g));
     } else {
         S::store((T*)v.out + off, time_update<MODE>(acc, ctr, prev, beta));
@@ -238,12 +229,10 @@ static inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t -
 
 template <int MODE, typename T, int R>
 static hipError_t point_nd(const ZView& v, const Coefs& w, const Box3& box, hipStream_t s) {
-    const int64_t total = box.n[0] * box.n[1] * box.n[2];
+    const int64_t total = box.n[1] * box.n[2];
     if (total == 0) return hipSuccess;
     const unsigned nb = blocks_for(total, 256);
-    if (v.g.nd == 3)
-        hipLaunchKernelGGL((k_point<MODE, R, T, 3>), dim3(nb), dim3(256), 0, s, v, w, box);
-    else if (v.g.nd == 2)
+    if (v.g.nd == 2)
         hipLaunchKernelGGL((k_point<MODE, R, T, 2>), dim3(nb), dim3(256), 0, s, v, w, box);
     else
         hipLaunchKernelGGL((k_point<MODE, R, T, 1>), dim3(nb), dim3(256), 0, s, v, w, box);
@@ -282,6 +271,11 @@ hipError_t launch_point(int mode, int radius, int dtype, const ZView& v, const C
 
 hipError_t launch_zmarch(int mode, int radius, int dtype, int cfg, const ZView& v, const Coefs& w, int parity,
                          int arow, int trow, hipStream_t s) {
+    if (cfg == kBrickCfg) {
+        Box3 all{};
+        for (int a = 0; a < 3; a++) all.n[a] = v.g.n[a];
+        return launch_brick(mode, radius, dtype, v.zc, v, w, all, parity, arow, trow, s);
+    }
     if (mode == MODE_WAVE_D || mode == MODE_WAVE_ADJ || mode == MODE_WAVE_ADJ2 || mode == MODE_WAVE_DAMP) {
         // the adjoint path and the absorbing layer are FP32 only
         if (dtype != DT_F32) return hipErrorInvalidValue;

@@ -148,12 +148,17 @@ inline constexpr int kNumTileCfgs = sizeof(kTileCfgs) / sizeof(kTileCfgs[0]);
 inline constexpr int kPersistentCfg = 1;
 // 64-bit words of its barrier, error flag and per-XCD ticket counters
 inline constexpr int kPersistentWords = 2 + 2 * 8;
+// The brick kernel (zbrick.hip) as one more tile shape of the launchers: a
+// 64 x 16 tile of 256 threads whose "z-chunk" is the brick's planes (2 or 4),
+// all loaded at once.
+inline constexpr int kBrickCfg = kNumTileCfgs;
+inline constexpr int kBrickTileX = 64, kBrickTileY = 16;
 // z-chunk lengths of the z-marching variants
 inline constexpr int kZChunks[] = {256, 128, 64, 32};
 inline constexpr int kNumZChunks = sizeof(kZChunks) / sizeof(kZChunks[0]);
 
-inline int tile_tx(int cfg) { return kTileCfgs[cfg].vx * kTileCfgs[cfg].bx; }
-inline int tile_ty(int cfg) { return kTileCfgs[cfg].by * kTileCfgs[cfg].vy; }
+inline int tile_tx(int cfg) { return cfg == kBrickCfg ? kBrickTileX : kTileCfgs[cfg].vx * kTileCfgs[cfg].bx; }
+inline int tile_ty(int cfg) { return cfg == kBrickCfg ? kBrickTileY : kTileCfgs[cfg].by * kTileCfgs[cfg].vy; }
 inline int tile_threads(int cfg) { return kTileCfgs[cfg].bx * kTileCfgs[cfg].by; }
 
 struct Box3 {
@@ -176,6 +181,11 @@ hipError_t launch_point(int mode, int radius, int dtype, const ZView& v, const C
                         hipStream_t s);
 hipError_t launch_zmarch(int mode, int radius, int dtype, int cfg, const ZView& v, const Coefs& w,
                          int parity, int arow, int trow, hipStream_t s);
+// the sweep of a box by bricks of bz planes; parity, arow, trow and the modes
+// as for launch_zmarch, which takes this kernel as tile shape kBrickCfg over
+// the whole interior with v.zc planes
+hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v, const Coefs& w, const Box3& box,
+                        int parity, int arow, int trow, hipStream_t s);
 // batched shots: d_block_map[2 b], d_block_map[2 b + 1] = shot and block within the shot of block b
 hipError_t launch_zmarch_batch(int radius, int dtype, int cfg, const ZView* d_views, const int* d_block_map,
                                int nblocks, const Coefs& w, int parity, int arow, int trow, hipStream_t s);

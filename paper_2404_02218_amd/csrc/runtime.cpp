@@ -155,7 +155,8 @@ struct DevTable {
     }
 };
 
-// Variant numbers: 0 = point kernel; 1 .. kNumZVariants = z-marching
+// Variant numbers: 0 = the brick kernel (3D) or the point kernel; 1 ..
+// kNumZVariants = z-marching
 // (tile shape, z-chunk); then the depth-2 temporally blocked sweep, one per
 // z-chunk, where the plan supports it.
 struct Variant {
@@ -191,10 +192,13 @@ Variant variant_of(int v) {
     return r;
 }
 
-// Default z-marching variant: the first tile shape, with the longest z-chunk
-// that still gives at least 4 workgroups per compute unit (256 CUs).
+// Default variant: the brick kernel (variant 0) up to 12M points, where the
+// z-march leaves compute units idle (one FP32 wave step, brick / the best
+// z-march: 128^3 7.9 / 24 us, 192^3 21 / 26, 224^3 33 / -, 256^3 47 / 44).
+// Past that the first z-marching tile shape, with the longest z-chunk that
+// still gives at least 4 workgroups per compute unit (256 CUs).
 int default_variant(const Layout& L) {
-    if (L.ndim != 3) return 0;
+    if (L.ndim != 3 || (int64_t)L.g.n[0] * L.g.n[1] * L.g.n[2] <= 12000000) return 0;
     const int cfg = 0;
     const int64_t ntx = (L.g.n[2] + tile_tx(cfg) - 1) / tile_tx(cfg);
     const int64_t nty = (L.g.n[1] + tile_ty(cfg) - 1) / tile_ty(cfg);
@@ -374,6 +378,18 @@ int variant_count_of(const stencil_plan_s* p) {
     return 1 + kNumZVariants + (tb_supported(p) ? kNumTB2ZChunks : 0);
 }
 
+// Planes per brick of the brick kernel over a box of n points.  Two keep the
+// most workgroups in flight; four read a level 3 times instead of 5 (radius
+// 4), which wins once the box is larger than the caches (512^3 FP32: 566 us a
+// step with 2, 463 with 4; 256^3: 47 and 51), and for 16-bit storage, whose
+// loads are half as wide, once four workgroups share a compute unit (207 x
+// 301 x 259: 33.3 and 31.3 us; 128^3: 6.4 and 6.6).
+int brick_planes(const int64_t* n, int dtype) {
+    const int64_t tiles = ((n[2] + kBrickTileX - 1) / kBrickTileX) * ((n[1] + kBrickTileY - 1) / kBrickTileY);
+    const bool many = dtype == STENCIL_F32 ? n[0] * n[1] * n[2] > (int64_t(1) << 25) : tiles * ((n[0] + 3) / 4) >= 1024;
+    return many ? 4 : 2;
+}
+
 // the batch variant that runs every shot with its own plan, concurrently
 bool batch_concurrent(const stencil_plan_s* p, int v) { return p->batch && v == variant_count_of(p) - 1; }
 
@@ -384,8 +400,17 @@ bool batch_persistent(const stencil_plan_s* p, int v) {
     return p->batch && v >= n - 1 - kNumPersistent && v < n - 1;
 }
 
-// variant v of plan p (batch plans add the persistent launches)
+// variant v of plan p (batch plans add the persistent launches; variant 0 of
+// a 3D sweep plan is the brick kernel)
 Variant plan_variant(const stencil_plan_s* p, int v) {
+    if (!p->batch && !p->program && p->ndim == 3 && v == 0) {
+        Variant r;
+        r.zmarch = true;
+        r.cfg = kBrickCfg;
+        const int64_t n[3] = {p->L.g.n[0], p->L.g.n[1], p->L.g.n[2]};
+        r.zc = brick_planes(n, p->dtype);
+        return r;
+    }
     if (!batch_persistent(p, v)) return variant_of(v);
     Variant r;
     r.zmarch = true;
@@ -556,6 +581,10 @@ void set_tiling(ZView& v, const Layout& L, const Variant& var) {
     v.ntx = (L.g.n[2] + TX - 1) / TX;
     v.nty = (L.g.n[1] + TY - 1) / TY;
     chunking(L.g.n[0], var.zc, v.zc, v.nzc);
+    if (var.cfg == kBrickCfg) {   // bricks keep their compiled number of planes
+        v.zc = var.zc;
+        v.nzc = (L.g.n[0] + var.zc - 1) / var.zc;
+    }
     if (L.g.n[0] == 0 || L.g.n[1] == 0 || L.g.n[2] == 0) v.ntx = v.nty = v.nzc = 0;
 }
 
@@ -802,7 +831,7 @@ stencil_status enqueue_run(stencil_plan p, void* a, void* b, const void* beta, i
                            const RunLists& RL, hipStream_t s) {
     const Layout& L = p->L;
     if (p->ndim == 2 && p->variant > 0 && heat2d_supported(p)) return enqueue_run_heat2d(p, a, b, nsteps, s);
-    Variant var = variant_of(p->variant);
+    Variant var = plan_variant(p, p->variant);
     const bool wave = p->kind == STENCIL_WAVE2;
     if (var.tb && wave) return enqueue_run_tb(p, var, a, b, beta, nsteps, RL, s);
     int64_t t0 = 0;
@@ -1067,7 +1096,11 @@ stencil_status stencil_apply(stencil_plan p, void* out, const void* const* in, c
     v.g = L.g;
     v.damp = p->damped ? (const float*)p->damp.buf.p : nullptr;
     const int mode = wave ? (p->damped ? MODE_WAVE_DAMP : MODE_WAVE) : MODE_HEAT;
-    HIP_TRY(launch_point(mode, p->radius, p->dtype, v, p->w, box, (hipStream_t)stream));
+    hipStream_t s = (hipStream_t)stream;
+    if (p->ndim == 3)
+        HIP_TRY(launch_brick(mode, p->radius, p->dtype, brick_planes(box.n, p->dtype), v, p->w, box, 0, 0, -1, s));
+    else
+        HIP_TRY(launch_point(mode, p->radius, p->dtype, v, p->w, box, s));
     return STENCIL_OK;
 }
 
@@ -1096,7 +1129,7 @@ static stencil_status run_args(stencil_plan p, void** fields, int64_t nsteps, co
 }
 
 static stencil_status prepare_points(stencil_plan p, const stencil_source* src, const stencil_receivers* rec) {
-    const Variant var = variant_of(p->variant);
+    const Variant var = plan_variant(p, p->variant);
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     ST_TRY(build_points(p->L, src ? src->n : 0, src ? src->pos : nullptr, cfg, p->src));
     if (var.tb) ST_TRY(build_points(p->L, src ? src->n : 0, src ? src->pos : nullptr, var.cfg, p->src_ext, 4));
@@ -1229,7 +1262,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     ST_TRY(check_source_scale(src));
     ST_TRY(check_workspace(p));
     const Layout& L = p->L;
-    const Variant var = variant_of(p->variant);
+    const Variant var = plan_variant(p, p->variant);
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
     HostPoints hs, he, hr;
@@ -2273,8 +2306,8 @@ stencil_status stencil_adjoint_workspace(stencil_plan p, int64_t nsteps, int64_t
 }
 
 static Variant adjoint_variant(stencil_plan p) {
-    Variant var = variant_of(p->variant);
-    if (!var.zmarch) var = variant_of(default_variant(p->L));
+    Variant var = plan_variant(p, p->variant);
+    if (!var.zmarch) var = plan_variant(p, default_variant(p->L));
     return var;
 }
 
@@ -2856,7 +2889,7 @@ static stencil_status time_batch_concurrent(stencil_plan p, void* const* fields,
     auto body = [&](hipStream_t bs, int sh) -> stencil_status {
         const stencil_plan_s* q = p->shot_plans[sh];
         const Layout& L = q->L;
-        const Variant var = variant_of(q->variant);
+        const Variant var = plan_variant(q, q->variant);
         char* out = (char*)scratch + off[sh];
         if (var.tb) {
             TBView t{};
@@ -2880,17 +2913,8 @@ static stencil_status time_batch_concurrent(stencil_plan p, void* const* fields,
             v.beta = fields[3 * sh + 2];
             v.out = out;
             v.g = L.g;
-            if (var.zmarch) {
-                set_tiling(v, L, var);
-                HIP_TRY(launch_zmarch(MODE_WAVE, q->radius, q->dtype, var.cfg, v, q->w, 0, 0, -1, bs));
-            } else {
-                Box3 box{};
-                for (int a = 0; a < 3; a++) {
-                    box.lo[a] = 0;
-                    box.n[a] = L.g.n[a];
-                }
-                HIP_TRY(launch_point(MODE_WAVE, q->radius, q->dtype, v, q->w, box, bs));
-            }
+            set_tiling(v, L, var);
+            HIP_TRY(launch_zmarch(MODE_WAVE, q->radius, q->dtype, var.cfg, v, q->w, 0, 0, -1, bs));
         }
         return STENCIL_OK;
     };

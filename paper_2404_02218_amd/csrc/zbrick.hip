@@ -1,0 +1,383 @@
+// The 3D sweep of a box by bricks (k_zbrick): a workgroup
+// computes a brick of 64 x 16 x BZ points.  Every load of the brick (the
+// threads' own z columns, the in-plane margins, u_prev and beta) is issued
+// before the first one is used and a single barrier separates them from the
+// arithmetic, so a workgroup pays the memory latency once, where the
+// z-marching kernel pays it again on every plane of its chunk.
+//
+// It serves what the z-march leaves idle: grids with too few xy tiles and
+// z-chunks to fill 256 compute units, and boxes (stencil_apply on the boundary
+// slabs and the interior of a decomposed grid).  It reads each level
+// (BZ + 2R) / BZ times in z, mostly from the caches, so on grids that fill the
+// chip the z-march, which reads it once, stays ahead.  Small grids are bound
+// by the launch and one memory latency, larger ones by the cache traffic.
+//
+// One FP32 wave step, radius 4, in us (this kernel / best z-march / one
+// thread per point with its taps from the caches, which this replaces):
+// 64^3 4.0 / 23 / -, 61 x 75 x 90 4.9 / 23 / 6.3 plus 3.9 of injection and
+// recording, 128^3 7.9 / 24 / 14, 192^3 21 / 26, 256^3 47 / 44, 512^3 463 /
+// 372.  FP16 207 x 301 x 259: 31 / 35.
+//
+// Each point takes the canonical operation order (device.hpp), so the results
+// are those of every other sweep kernel bit for bit.
+#include "zmarch.hpp"
+
+namespace stn {
+
+namespace {
+
+// Number the bricks z first where the planes that z neighbours share pass the
+// reach of an XCD's 4 MB L2 otherwise: neighbours in z share 2R of their
+// BZ + 2R planes, tiles side by side only their margins.  One wave step in
+// us, x first / z first: 64 x 512 x 512 77 / 51, 207 x 301 x 259 60 / 55 (3.1
+// MB), 256^3 47 / 54 (2.6 MB), 224^3 33 / 39.  Past 2^25 points the order x
+// first streams better again (512^3, BZ = 4: 463 / 505).
+bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz) {
+    const double plane = (double)n[1] * n[2];
+    return (bz + 2 * radius) * plane * esize > 2.85e6 && plane * n[0] <= (double)(1 << 25);
+}
+
+template <int R, int BZ>
+struct ZBrick {
+    static constexpr int NT = 256, TX = kBrickTileX, TY = kBrickTileY;
+    static constexpr int LDX = TX + 8, LDY = TY + 2 * R, PLANE = LDX * LDY;
+    // margin groups of a plane: one each side of every tile row, TX / 4 per
+    // row above and below the tile
+    static constexpr int NHX = 2 * TY, NHP = NHX + 2 * R * (TX / 4), NHT = NHP * BZ, NH = (NHT + NT - 1) / NT;
+    static constexpr int NQ = BZ + 2 * R;   // planes of a thread's own column
+    // sources of the brick staged at a time: position and amount
+    static constexpr int NS = 64;
+    static_assert(NT == (TX / 4) * TY, "one 4-point group of the tile per thread");
+};
+
+template <int MODE>
+inline constexpr bool kAdj = MODE == MODE_WAVE_ADJ || MODE == MODE_WAVE_ADJ2;
+
+// waves per SIMD the registers are held to (the heat form would otherwise
+// read the taps of every plane ahead and take 216 registers at BZ = 4)
+template <int MODE, int BZ>
+inline constexpr int kBrickWaves = BZ == 2 ? 5 : kAdj<MODE> ? 3 : 4;
+
+// zfast: workgroups are numbered z first, then x, y (else x, y, z)
+template <int MODE, int R, typename T, int BZ>
+__global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, int zfast, int parity,
+                                                                       int arow, int trow) {
+    using Z = ZBrick<R, BZ>;
+    using S = Storage<T>;
+    constexpr int NT = Z::NT, TX = Z::TX, TY = Z::TY, LDX = Z::LDX, PLANE = Z::PLANE, NH = Z::NH, NQ = Z::NQ;
+    constexpr bool WAVE = MODE != MODE_HEAT;
+    constexpr bool ADJ = kAdj<MODE>, ADJ2 = MODE == MODE_WAVE_ADJ2;
+    __shared__ __attribute__((aligned(16))) float lds[BZ * PLANE];
+    __shared__ double src_amt[Z::NS];
+    __shared__ int src_at[Z::NS];
+
+    const int tid = threadIdx.x, tx = tid % (TX / 4), ty = tid / (TX / 4);
+    const int lb = xcd_remap(blockIdx.x, gridDim.x);
+    int zch, tile;
+    if (zfast) {
+        zch = lb % v.nzc;
+        tile = lb / v.nzc;
+    } else {
+        zch = lb / (v.ntx * v.nty);
+        tile = lb % (v.ntx * v.nty);
+    }
+    const int tile_x = tile % v.ntx, tile_y = tile / v.ntx;
+    // the box's x origin rounded down to a 4-element group keeps every access aligned
+    const int bx = (int)box.lo[2], by = (int)box.lo[1], bz = (int)box.lo[0];
+    const int X0 = (bx & ~3) + tile_x * TX, Y0 = by + tile_y * TY, zb = bz + zch * BZ;
+    const int xe = bx + (int)box.n[2], ye = by + (int)box.n[1], ze = min(zb + BZ, bz + (int)box.n[0]);
+    const int64_t sz = v.g.s[0], sy = v.g.s[1];
+
+    const T* U = (const T*)(parity ? v.prev : v.u) + v.g.origin;
+    const T* P = (const T*)(parity ? v.u : v.prev) + v.g.origin;
+    T* O = (T*)(parity ? (void*)v.u : v.out) + v.g.origin;
+    const T* B = (const T*)v.beta + v.g.origin;
+
+    // receivers sample the input level (read-only during this launch)
+    if (trow >= 0 && lb == 0) {
+        for (int r = tid; r < v.rec.n; r += NT)
+            v.rec.trace[(int64_t)trow * v.rec.n + r] = (double)S::load(U + v.rec.off[r]);
+    }
+
+    // every load stays inside the field: planes and rows are clamped to the
+    // R-deep halo, x groups to the row; clamped values feed no stored point
+    const int xmax4 = (int)(v.g.rowlen - v.g.xlead) - 4;
+    const int ymax = v.g.n[1] + R - 1, zmax = v.g.n[0] + R - 1;
+    const int x0 = X0 + 4 * tx, y = Y0 + ty;
+    const T* own = U + (int64_t)min(y, ymax) * sy + min(x0, xmax4);
+    const int64_t own_off = own - U;
+
+    // the margins of planes zb .. zb + BZ - 1 and the thread's own column of
+    // planes zb - R .. zb + BZ + R - 1, in the storage type while in flight
+    using Raw = typename RawGroup<T>::type;
+    Raw hal[NH], rq[NQ], rp[BZ], rb[BZ];
+    int hlds[NH];
+#pragma unroll
+    for (int k = 0; k < NQ; k++) rq[k] = load4_raw<T, false>(own + (int64_t)min(zb - R + k, zmax) * sz);
+#pragma unroll
+    for (int m = 0; m < NH; m++) {
+        const int h = min(tid + m * NT, Z::NHT - 1), p = h / Z::NHP, i = h % Z::NHP;
+        int hy, hx, l;
+        if (i < Z::NHX) {
+            const int r = i >> 1, side = i & 1;
+            hy = Y0 + r;
+            hx = side ? X0 + TX : X0 - 4;
+            l = (R + r) * LDX + (side ? 4 + TX : 0);
+        } else {
+            const int r = (i - Z::NHX) / (TX / 4), g = (i - Z::NHX) % (TX / 4);
+            hy = r < R ? Y0 - R + r : Y0 + TY + (r - R);
+            hx = X0 + 4 * g;
+            l = (r < R ? r : TY + r) * LDX + 4 + 4 * g;
+        }
+        hlds[m] = p * PLANE + l;
+        hal[m] = load4_raw<T, false>(U + (int64_t)min(zb + p, zmax) * sz + (int64_t)min(hy, ymax) * sy + min(hx, xmax4));
+    }
+    if constexpr (WAVE) {
+#pragma unroll
+        for (int p = 0; p < BZ; p++) {
+            const int64_t zo = (int64_t)min(zb + p, zmax) * sz;
+            rp[p] = load4_raw<T, false>(P + zo + own_off);
+            rb[p] = load4_raw<T, false>(B + zo + own_off);
+        }
+    }
+    // adjoint: the second differences and the imaging partial of the groups
+    // that lie wholly inside the interior (others read them at the store)
+    const int64_t cell = v.g.origin + (int64_t)y * sy + x0;
+    const bool full = x0 >= bx && x0 + 3 < xe;
+    const bool gload = ADJ && !v.gfresh;
+    float4 cd[BZ], cg[BZ], cd2[BZ];
+    if constexpr (ADJ) {
+#pragma unroll
+        for (int p = 0; p < BZ; p++)
+            if (y < ye && full && zb + p < ze) {
+                const int64_t o = cell + (int64_t)(zb + p) * sz;
+                cd[p] = Storage<float>::load4_nt(v.dfield + o);
+                cg[p] = gload ? Storage<float>::load4(v.gfield + o) : make_float4(0.f, 0.f, 0.f, 0.f);
+                if constexpr (ADJ2) cd2[p] = Storage<float>::load4_nt(v.dfield2 + o);
+            }
+    }
+    float dgy = 0.f, dgx[4];
+    if constexpr (MODE == MODE_WAVE_DAMP) {
+        const float* D = v.damp + v.g.n[0];
+        dgy = D[min(y, v.g.n[1] - 1)];
+#pragma unroll
+        for (int i = 0; i < 4; i++) dgx[i] = D[v.g.n[1] + min(x0 + i, v.g.n[2] - 1)];
+    }
+
+    // the tile's sources in this brick: entries s0 .. s1 - 1 of its z-sorted list
+    int s0 = 0, s1 = 0;
+    if (v.src.n > 0) {
+        const int begin = ld_inv(v.src.tile_begin + tile), end = ld_inv(v.src.tile_begin + tile + 1);
+        s0 = s1 = begin;
+        // counted by the lanes of a wave, 64 entries at a time: a walk or a
+        // search would put a chain of loads before the compute
+        for (int from = begin; from < end; from += 64) {
+            const int e = from + (tid & 63);
+            const int z = e < end ? v.src.zyx4[4 * e] : INT_MAX;
+            s0 += __popcll(__ballot(z < zb));
+            s1 += __popcll(__ballot(z < ze));
+        }
+    }
+    // up to NS of them at a time go through LDS, one per thread, so that many
+    // sources in one brick (a receiver line of the adjoint) cost one latency
+    auto stage_sources = [&](int from) {
+        const int e = from + tid;
+        if (tid < Z::NS && e < s1) {
+            const int* q = v.src.zyx4 + 4 * e;
+            src_amt[tid] = v.src.amp[(int64_t)arow * v.src.n + q[3]] * (v.src.scale ? v.src.scale[q[3]] : 1.0);
+            src_at[tid] = ((q[0] - zb) * TY + (q[1] - Y0)) * TX + (q[2] - X0);
+        }
+    };
+    if (s0 < s1) stage_sources(s0);
+
+    float4 q[NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; k++) q[k] = widen4<T>(rq[k]);
+#pragma unroll
+    for (int p = 0; p < BZ; p++)
+        *reinterpret_cast<float4*>(&lds[p * PLANE + (R + ty) * LDX + 4 + 4 * tx]) = q[R + p];
+#pragma unroll
+    for (int m = 0; m < NH; m++)
+        if (tid + m * NT < Z::NHT) *reinterpret_cast<float4*>(&lds[hlds[m]]) = widen4<T>(hal[m]);
+    __syncthreads();
+
+    float o[BZ][4], dv[BZ][4];
+#pragma unroll
+    for (int p = 0; p < BZ; p++) {
+        const float* L = lds + p * PLANE + (R + ty) * LDX + 4 + 4 * tx;
+        const float4 c = q[R + p];
+        float acc[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) acc[i] = w.cd0 * comp(c, i);
+#pragma unroll
+        for (int k = 1; k <= R; k++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc[i] = fmaf(w.c[k], comp(q[R + p - k], i) + comp(q[R + p + k], i), acc[i]);
+#pragma unroll
+        for (int k = 1; k <= R; k++) {
+            const float4 m = *reinterpret_cast<const float4*>(L - k * LDX);
+            const float4 n = *reinterpret_cast<const float4*>(L + k * LDX);
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc[i] = fmaf(w.c[k], comp(m, i) + comp(n, i), acc[i]);
+        }
+        const float4 xl = *reinterpret_cast<const float4*>(L - 4);
+        const float4 xr = *reinterpret_cast<const float4*>(L + 4);
+        const float xv[12] = {xl.x, xl.y, xl.z, xl.w, c.x, c.y, c.z, c.w, xr.x, xr.y, xr.z, xr.w};
+        float4 cp = make_float4(0.f, 0.f, 0.f, 0.f), cb = cp;
+        if constexpr (WAVE) {
+            cp = widen4<T>(rp[p]);
+            cb = widen4<T>(rb[p]);
+        }
+        float dgz = 0.f;
+        if constexpr (MODE == MODE_WAVE_DAMP) dgz = v.damp[min(zb + p, v.g.n[0] - 1)];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            float m[R], n[R];
+#pragma unroll
+            for (int k = 1; k <= R; k++) {
+                m[k - 1] = xv[4 + i - k];
+                n[k - 1] = xv[4 + i + k];
+            }
+            const float a = axis_sum<R>(acc[i], w, m, n);
+            if constexpr (MODE == MODE_WAVE_DAMP)
+                o[p][i] = damped_update(a, comp(c, i), comp(cp, i), comp(cb, i), (dgz + dgy) + dgx[i]);
+            else
+                o[p][i] = time_update<MODE>(a, comp(c, i), comp(cp, i), comp(cb, i));
+            if constexpr (MODE == MODE_WAVE_D) dv[p][i] = comp(cb, i) * a;
+        }
+    }
+
+    for (int from = s0; from < s1;) {
+        const int cnt = min(s1 - from, Z::NS);
+        for (int e = 0; e < cnt; e++) {
+            const int at = src_at[e];
+            if ((at / TX) % TY == ty && (at % TX) >> 2 == tx) {
+#pragma unroll
+                for (int p = 0; p < BZ; p++)
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+                        if (at == (p * TY + ty) * TX + 4 * tx + i) {
+                            o[p][i] = inject<T>(o[p][i], src_amt[e]);
+                            if constexpr (MODE == MODE_WAVE_D) dv[p][i] = (float)((double)dv[p][i] + src_amt[e]);
+                        }
+            }
+        }
+        from += cnt;
+        if (from < s1) {
+            __syncthreads();
+            stage_sources(from);
+            __syncthreads();
+        }
+    }
+
+    if (y >= ye || x0 >= xe) return;
+#pragma unroll
+    for (int p = 0; p < BZ; p++) {
+        if (zb + p >= ze) break;
+        const int64_t off = (int64_t)(zb + p) * sz + (int64_t)y * sy + x0;
+        if (full) {
+            S::store4(O + off, make_float4(o[p][0], o[p][1], o[p][2], o[p][3]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (x0 + i >= bx && x0 + i < xe) S::store(O + off + i, o[p][i]);
+        }
+        if constexpr (MODE == MODE_WAVE_D) {
+            float* D = v.dfield + v.g.origin + off;
+            if (full) {
+                Storage<float>::store4_nt(D, make_float4(dv[p][0], dv[p][1], dv[p][2], dv[p][3]));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (x0 + i < xe) D[i] = dv[p][i];
+            }
+        }
+        // the input level's term first (ADJ2), as two one-level steps would
+        if constexpr (ADJ) {
+            float* G = v.gfield + v.g.origin + off;
+            if (full) {
+                float g[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    g[i] = comp(cg[p], i);
+                    if constexpr (ADJ2) g[i] = fmaf(comp(q[R + p], i), comp(cd2[p], i), g[i]);
+                    g[i] = fmaf(o[p][i], comp(cd[p], i), g[i]);
+                }
+                Storage<float>::store4(G, make_float4(g[0], g[1], g[2], g[3]));
+            } else {
+                const float* D = v.dfield + v.g.origin + off;
+                const float* D2 = v.dfield2 + v.g.origin + off;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (x0 + i < xe) {
+                        float g = gload ? G[i] : 0.f;
+                        if constexpr (ADJ2) g = fmaf(comp(q[R + p], i), D2[i], g);
+                        G[i] = fmaf(o[p][i], D[i], g);
+                    }
+            }
+        }
+    }
+}
+
+template <int MODE, int R, typename T, int BZ>
+hipError_t brick_launch(const ZView& v, const Coefs& w, const Box3& box, int parity, int arow, int trow, hipStream_t s) {
+    ZView b = v;
+    b.ntx = (int)(((box.lo[2] & 3) + box.n[2] + kBrickTileX - 1) / kBrickTileX);
+    b.nty = (int)((box.n[1] + kBrickTileY - 1) / kBrickTileY);
+    b.nzc = (int)((box.n[0] + BZ - 1) / BZ);
+    const int64_t nb = (int64_t)b.ntx * b.nty * b.nzc;
+    if (nb == 0) return hipSuccess;
+    if (nb > INT_MAX) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((k_zbrick<MODE, R, T, BZ>), dim3((unsigned)nb), dim3(256), 0, s, b, w, box,
+                       (int)brick_zfast(box.n, R, sizeof(T), BZ), parity, arow, trow);
+    return hipGetLastError();
+}
+
+template <int MODE, int R, typename T>
+hipError_t brick_z(int bz, const ZView& v, const Coefs& w, const Box3& box, int parity, int arow, int trow,
+                   hipStream_t s) {
+    if (bz == 2) return brick_launch<MODE, R, T, 2>(v, w, box, parity, arow, trow, s);
+    if (bz == 4) return brick_launch<MODE, R, T, 4>(v, w, box, parity, arow, trow, s);
+    return hipErrorInvalidValue;
+}
+
+template <int MODE, typename T>
+hipError_t brick_r(int radius, int bz, const ZView& v, const Coefs& w, const Box3& box, int parity, int arow, int trow,
+                   hipStream_t s) {
+    switch (radius) {
+        case 1: return brick_z<MODE, 1, T>(bz, v, w, box, parity, arow, trow, s);
+        case 2: return brick_z<MODE, 2, T>(bz, v, w, box, parity, arow, trow, s);
+        case 3: return brick_z<MODE, 3, T>(bz, v, w, box, parity, arow, trow, s);
+        case 4: return brick_z<MODE, 4, T>(bz, v, w, box, parity, arow, trow, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t brick_m(int mode, int radius, int bz, const ZView& v, const Coefs& w, const Box3& box, int parity, int arow,
+                   int trow, hipStream_t s) {
+    if (mode == MODE_HEAT) return brick_r<MODE_HEAT, T>(radius, bz, v, w, box, parity, arow, trow, s);
+    if (mode == MODE_WAVE) return brick_r<MODE_WAVE, T>(radius, bz, v, w, box, parity, arow, trow, s);
+    // the adjoint path and the absorbing layer are FP32 only
+    if constexpr (std::is_same<T, float>::value) {
+        if (mode == MODE_WAVE_D) return brick_r<MODE_WAVE_D, T>(radius, bz, v, w, box, parity, arow, trow, s);
+        if (mode == MODE_WAVE_ADJ) return brick_r<MODE_WAVE_ADJ, T>(radius, bz, v, w, box, parity, arow, trow, s);
+        if (mode == MODE_WAVE_ADJ2) return brick_r<MODE_WAVE_ADJ2, T>(radius, bz, v, w, box, parity, arow, trow, s);
+        if (mode == MODE_WAVE_DAMP) return brick_r<MODE_WAVE_DAMP, T>(radius, bz, v, w, box, parity, arow, trow, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v, const Coefs& w, const Box3& box,
+                        int parity, int arow, int trow, hipStream_t s) {
+    switch (dtype) {
+        case DT_F32: return brick_m<float>(mode, radius, bz, v, w, box, parity, arow, trow, s);
+        case DT_BF16: return brick_m<bf16>(mode, radius, bz, v, w, box, parity, arow, trow, s);
+        case DT_F16: return brick_m<f16>(mode, radius, bz, v, w, box, parity, arow, trow, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace stn
