@@ -171,7 +171,8 @@ stencil_status stencil_apply(stencil_plan plan, void* out, const void* const* in
  * other than 0 they are enqueued directly instead (the same kernels and
  * bits).  The temporally blocked wave variants need a caller workspace
  * (stencil_run_workspace / stencil_set_workspace); without one the call
- * fails with STENCIL_E_STATE.  The plan keeps small device tables of
+ * fails with STENCIL_E_STATE.  A large 2D wave plan takes several steps per
+ * launch with one, and one without.  The plan keeps small device tables of
  * positions and, for sources with scales, their formed amounts; it never
  * allocates field memory. */
 stencil_status stencil_run(stencil_plan plan, void** fields, int64_t nsteps, const stencil_source* src,
@@ -522,7 +523,8 @@ stencil_status stencil_schedule(const stencil_step* steps, int nsteps, int nfiel
 /* Bytes of caller workspace the plan's current variant needs in stencil_run
  * (stencil_batch_run for a batch): the second level pair of the temporally
  * blocked wave sweep (two fields, one pair per shot for a batch; Section 7
- * related work on overlapped temporal blocking), 0 for every other variant.
+ * related work on overlapped temporal blocking), and of large 2D wave plans,
+ * which also run without it; 0 for every other variant.
  * Query again after stencil_tune or stencil_set_variant. */
 stencil_status stencil_run_workspace(stencil_plan plan, size_t* bytes);
 
@@ -573,8 +575,10 @@ stencil_status stencil_check(stencil_plan plan, void* const* fields, stencil_che
 /* Kernel variants of a plan (this library's kernel choices: no passage of
  * the paper; the temporally blocked ones follow the overlapped temporal
  * blocking of Section 7's related work).  Variant 0, "point", is the
- * general kernel: one thread per point in 1D and 2D, bricks of 64 x 16 x 2 or
- * 4 points in 3D (the fastest there on grids too small for the others).
+ * general kernel: one thread per point in 1D, strips of 256 points in 2D (with
+ * several steps per launch on large grids with the zero halo), bricks of
+ * 64 x 16 x 2 or 4 points in 3D (the fastest there on grids too small for the
+ * others).
  * 3D plans add the z-marching sweep (tile shape and z-chunk), and for the
  * radius-4 wave and the FP32 heat with the zero halo the depth-2 temporally
  * blocked sweep (two steps per launch).  2D FP32 heat plans with the zero

@@ -48,6 +48,8 @@ struct RecList {
     int n;
     const int64_t* off;  // element offsets from the interior origin
     double* trace;       // [rows][n]
+    const int* zyx4;        // 2D strips: (z, y, x, index) by strip and row
+    const int* tile_begin;  // CSR over strips
 };
 
 // One field set as the sweep kernels see it.  For in-place wave steps
@@ -86,6 +88,30 @@ struct TBView {
     RecList rec;
     const float* damp;  // MODE_WAVE_DAMP: per-axis damping [n0 | n1 | n2]
     uint32_t range;   // bytes of each field's allocation (< 2^31)
+};
+
+// One pass of the 2D sweep: strips of 256 points along x, of which the wave
+// stores `width` (after `margin` on the left), and for several steps chunks of
+// `rows` rows (the launcher sets them).
+// u, prev: the levels read; out, out1: the newest level written and, for a
+// wave pass of several steps, the one before.  A one-step wave pass may
+// write over prev.  halo_even, halo_odd: the buffers that hold the halos of
+// the level u and of the next one.  src: every strip's sources, margins
+// included; rec: its own receivers; both by strip and row.
+inline constexpr int kMarchRowSources = 16;   // most sources a strip may have in one row
+struct M2View {
+    const void* u;
+    const void* prev;
+    const void* beta;
+    void* out;
+    void* out1;
+    const void* halo_even;
+    const void* halo_odd;
+    const float* damp;
+    Grid3 g;
+    int nstrips, nchunks, rows, width, margin;
+    SrcList src;
+    RecList rec;
 };
 
 // A stencil program: nout outputs, each a sum in program order of terms
@@ -186,6 +212,10 @@ hipError_t launch_zmarch(int mode, int radius, int dtype, int cfg, const ZView& 
 // the whole interior with v.zc planes
 hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v, const Coefs& w, const Box3& box,
                         int parity, int arow, int trow, hipStream_t s);
+// nt (1, 4; 8 for FP32 and radius 1) steps of the 2D sweep (march2d.hip); steps
+// use amplitude and trace rows row0 .. row0 + nt - 1
+hipError_t launch_march2d(int mode, int radius, int dtype, int nt, const M2View& v, const Coefs& w, int row0,
+                          hipStream_t s);
 // batched shots: d_block_map[2 b], d_block_map[2 b + 1] = shot and block within the shot of block b
 hipError_t launch_zmarch_batch(int radius, int dtype, int cfg, const ZView* d_views, const int* d_block_map,
                                int nblocks, const Coefs& w, int parity, int arow, int trow, hipStream_t s);

@@ -163,6 +163,7 @@ struct Variant {
     bool zmarch = false;
     bool tb = false;   // depth-2 temporal blocking (tile 64 x 32 = tile shape 0)
     bool persistent = false;   // batch: every step in one launch with grid barriers
+    bool march2d = false;      // the 2D sweep by strips
     int cfg = 0;
     int zc = 0;
 };
@@ -248,6 +249,7 @@ struct PointTables {
     DevTable grp, gbeg;           // entries grouped by position (point-kernel injection)
     int n = 0, ngrp = 0;
     int cfg = -1;
+    bool dense = false;
 };
 
 struct stencil_plan_s {
@@ -411,6 +413,11 @@ Variant plan_variant(const stencil_plan_s* p, int v) {
         r.zc = brick_planes(n, p->dtype);
         return r;
     }
+    if (!p->batch && !p->program && p->ndim == 2 && v == 0) {
+        Variant r;
+        r.march2d = true;
+        return r;
+    }
     if (!batch_persistent(p, v)) return variant_of(v);
     Variant r;
     r.zmarch = true;
@@ -478,6 +485,7 @@ void zyx_of(const Layout& L, const int64_t* p3, int out[3]) {
 struct HostPoints {
     int n = 0, ngrp = 0;
     bool tiled = false;
+    bool dense = false;   // 2D strips: more than kMarchRowSources points in a row of a strip
     std::vector<int64_t> off;
     std::vector<int> grp, gbeg, zyx4, tiles;
 };
@@ -527,11 +535,57 @@ void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPo
     for (size_t t = 1; t < H.tiles.size(); t++) H.tiles[t] += H.tiles[t - 1];
 }
 
-// Build the device tables of a point list (host_points, uploaded to the
-// plan's tables).
-stencil_status build_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, PointTables& T, int ext = 0) {
-    HostPoints H;
-    host_points(L, n, pos, cfg, H, ext);
+// Strips of the 2D sweep: a wave covers 256 points, of which it stores those
+// at least the deepest pass's reach away from either end.
+int march_margin(int radius) { return (int)round_up(radius * (radius == 1 ? 8 : 4), 4); }
+int march_width(int radius) { return 256 - 2 * march_margin(radius); }
+
+// Steps per pass of the 2D sweep: one, unless the grid is so large that the
+// memory traffic a deeper pass saves outweighs the rows it computes twice.
+// Below these points (in millions; by storage, kind and radius) the levels sit
+// in the caches and a pass of four is slower than four steps.  us a step at
+// 2048^2 / 4096^2 / 8192^2, one step and four (eight): FP32 wave r = 4 12.4,
+// 17.4 / 39, 36 / 213, 109; r = 1 11.5, 7.0 (6.3) / 38, 22 (15) / 208, 83
+// (51); FP32 heat r = 4 8.3, 16 / 23, 31 / 132, 100; FP16 heat r = 1 4.9, 5.4
+// / 11.8, 10.0 / 46, 30; BF16 wave r = 4 7.3, 18 / 21, 33 / 109, 100.
+int march_steps(int kind, int dtype, int radius, const Layout& L) {
+    static const double four[2][2][4] = {{{1.2, 6, 20, 24}, {0.9, 3, 5, 9}},       // FP32: heat, wave
+                                         {{8, 50, 100, 100}, {6, 14, 45, 60}}};    // 16 bits
+    const double pts = (double)L.g.n[1] * L.g.n[2] * 1e-6;
+    if (dtype == STENCIL_F32 && radius == 1 && pts >= 4) return 8;
+    return pts >= four[dtype != STENCIL_F32][kind == STENCIL_WAVE2][radius - 1] ? 4 : 1;
+}
+
+// As host_points, with the lists by strip of the 2D sweep and by row, each
+// point under every strip whose stored points, widened by ext, hold it.
+void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, HostPoints& H, int ext) {
+    host_points(L, n, pos, -1, H);
+    H.tiled = true;
+    const int W = march_width(radius), ns = std::max(1, (L.g.n[2] + W - 1) / W);
+    std::vector<std::tuple<int, int, int>> order;   // (strip, y, index)
+    for (int64_t i = 0; i < n; i++) {
+        int zyx[3];
+        zyx_of(L, pos + 3 * i, zyx);
+        const int s0 = std::max(0, (zyx[2] - ext) / W), s1 = std::min(ns - 1, (zyx[2] + ext) / W);
+        for (int k = s0; k <= s1; k++) order.emplace_back(k, zyx[1], (int)i);
+    }
+    std::stable_sort(order.begin(), order.end());
+    H.zyx4.assign(std::max<size_t>(4 * order.size(), 4), 0);
+    H.tiles.assign((size_t)ns + 1, 0);
+    for (size_t k = 0; k < order.size(); k++) {
+        const int i = std::get<2>(order[k]);
+        zyx_of(L, pos + 3 * i, &H.zyx4[4 * k]);
+        H.zyx4[4 * k + 3] = i;
+        H.tiles[std::get<0>(order[k]) + 1]++;
+        const size_t back = kMarchRowSources;
+        H.dense |= k >= back && std::get<0>(order[k]) == std::get<0>(order[k - back]) &&
+                   std::get<1>(order[k]) == std::get<1>(order[k - back]);
+    }
+    for (size_t t = 1; t < H.tiles.size(); t++) H.tiles[t] += H.tiles[t - 1];
+}
+
+// Upload a point list to a plan's tables.
+stencil_status upload_points(const HostPoints& H, int64_t n, int cfg, PointTables& T) {
     T.n = H.n;
     T.ngrp = H.ngrp;
     ST_TRY(T.off.upload(H.off.data(), sizeof(int64_t) * (size_t)n));
@@ -543,7 +597,15 @@ stencil_status build_points(const Layout& L, int64_t n, const int64_t* pos, int 
         ST_TRY(T.tiles.upload(H.tiles.data(), sizeof(int) * H.tiles.size()));
     }
     T.cfg = cfg;
+    T.dense = H.dense;
     return STENCIL_OK;
+}
+
+// Build the device tables of a point list.
+stencil_status build_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, PointTables& T, int ext = 0) {
+    HostPoints H;
+    host_points(L, n, pos, cfg, H, ext);
+    return upload_points(H, n, cfg, T);
 }
 
 SrcList src_list(const PointTables& T, const double* amp, const double* scale) {
@@ -565,6 +627,8 @@ RecList rec_list(const PointTables& T, double* trace) {
     r.n = T.n;
     r.off = (const int64_t*)T.off.buf.p;
     r.trace = trace;
+    r.zyx4 = (const int*)T.zyx4.buf.p;
+    r.tile_begin = (const int*)T.tiles.buf.p;
     return r;
 }
 
@@ -718,6 +782,7 @@ void periodic_copies(const Layout& L, int radius, std::vector<CopyList>& out) {
 struct RunLists {
     SrcList st, se;
     RecList rl;
+    bool dense = false;   // 2D: too many sources in a row for passes of several steps
 };
 
 RunLists plan_lists(stencil_plan p, const stencil_source* src, const stencil_receivers* rec) {
@@ -725,6 +790,7 @@ RunLists plan_lists(stencil_plan p, const stencil_source* src, const stencil_rec
     r.st = src_list(p->src, src ? src->amp : nullptr, nullptr);
     r.se = src_list(p->src_ext, src ? src->amp : nullptr, nullptr);
     r.rl = rec_list(p->rec, rec ? rec->trace : nullptr);
+    r.dense = p->src_ext.dense;
     return r;
 }
 
@@ -826,6 +892,63 @@ static stencil_status enqueue_run_heat2d(stencil_plan p, void* a, void* b, int64
     return STENCIL_OK;
 }
 
+// nt steps of the 2D sweep in one launch, from level u (and prev) to out (and
+// out1); he and ho hold the halos of level u and of the next one.
+static hipError_t march_pass(const stencil_plan_s* p, int nt, const void* u, const void* prev, const void* beta,
+                             void* out, void* out1, const void* he, const void* ho, const RunLists& RL, int64_t row0,
+                             hipStream_t s) {
+    const Layout& L = p->L;
+    M2View v{};
+    v.u = u;
+    v.prev = prev;
+    v.beta = beta;
+    v.out = out;
+    v.out1 = out1;
+    v.halo_even = he;
+    v.halo_odd = ho;
+    v.damp = p->damped ? (const float*)p->damp.buf.p : nullptr;
+    v.g = L.g;
+    v.width = march_width(p->radius);
+    v.margin = march_margin(p->radius);
+    v.nstrips = (L.g.n[2] + v.width - 1) / v.width;
+    v.src = RL.se;
+    v.rec = RL.rl;
+    const int mode = p->kind == STENCIL_WAVE2 ? (p->damped ? MODE_WAVE_DAMP : MODE_WAVE) : MODE_HEAT;
+    return launch_march2d(mode, p->radius, p->dtype, nt, v, p->w, (int)row0, s);
+}
+
+// 2D run by strips.  Passes of several steps read one buffer set and write
+// another: the two level buffers of a heat plan, the caller's pair and the
+// workspace pair (if one is attached) of a wave plan.  They come in even
+// numbers, so the newest level ends in a, as after plain steps; plain steps in
+// place make up the rest.
+static stencil_status enqueue_run_march2d(stencil_plan p, void* a, void* b, const void* beta, int64_t nsteps,
+                                          const RunLists& RL, hipStream_t s) {
+    const Layout& L = p->L;
+    const bool wave = p->kind == STENCIL_WAVE2;
+    int64_t t = 0;
+    if (p->bc == STENCIL_BC_DIRICHLET0 && !RL.dense) {
+        const size_t fb = (size_t)round_up(L.bytes, 256);
+        void* const w0 = p->ws;
+        void* const w1 = p->ws ? (char*)p->ws + fb : nullptr;
+        const int deepest = wave && p->ws_bytes < 2 * fb ? 1 : march_steps(p->kind, p->dtype, p->radius, L);
+        for (int nt = deepest; nt >= 4; nt /= 2)
+            for (; nsteps - t >= 2 * nt; t += 2 * nt) {
+                HIP_TRY(march_pass(p, nt, a, b, beta, wave ? w0 : b, w1, a, b, RL, t, s));
+                HIP_TRY(march_pass(p, nt, wave ? w0 : b, w1, beta, a, b, a, b, RL, t + nt, s));
+            }
+    }
+    std::vector<CopyList> per;
+    if (p->bc == STENCIL_BC_PERIODIC) periodic_copies(L, p->radius, per);
+    for (int64_t done = t; t < nsteps; t++) {
+        void* const cur = ((t - done) & 1) ? b : a;
+        void* const nxt = cur == a ? b : a;
+        for (const CopyList& cl : per) HIP_TRY(launch_boxcopy(p->dtype, COPY_FIELD, cur, L.g, L.offset, cl, nullptr, s));
+        HIP_TRY(march_pass(p, 1, cur, nxt, beta, nxt, nullptr, cur, nxt, RL, t, s));
+    }
+    return STENCIL_OK;
+}
+
 // Enqueue nsteps sweeps of a single plan (no capture logic here).
 stencil_status enqueue_run(stencil_plan p, void* a, void* b, const void* beta, int64_t nsteps,
                            const RunLists& RL, hipStream_t s) {
@@ -833,6 +956,7 @@ stencil_status enqueue_run(stencil_plan p, void* a, void* b, const void* beta, i
     if (p->ndim == 2 && p->variant > 0 && heat2d_supported(p)) return enqueue_run_heat2d(p, a, b, nsteps, s);
     Variant var = plan_variant(p, p->variant);
     const bool wave = p->kind == STENCIL_WAVE2;
+    if (var.march2d) return enqueue_run_march2d(p, a, b, beta, nsteps, RL, s);
     if (var.tb && wave) return enqueue_run_tb(p, var, a, b, beta, nsteps, RL, s);
     int64_t t0 = 0;
     if (var.tb) {
@@ -1034,7 +1158,10 @@ stencil_status stencil_create(stencil_plan* out, stencil_kind kind, int ndim, co
         return st;
     }
     p->variant = default_variant(p->L);
-    if (heat2d_supported(p)) p->variant = 2;   // 8 steps per launch on 16 x 16 tiles
+    // 2D heat: 8 steps per launch on 16 x 16 tiles in LDS, until the sweep by
+    // strips passes it (us a step, tiles / strips: r = 1 700^2 2.3 / 2.8, 1000^2
+    // 3.7 / 3.4, 2048^2 13 / 5.0; r = 2 512^2 2.0 / 2.9, 700^2 3.4 / 3.0)
+    if (heat2d_supported(p)) p->variant = p->L.g.n[1] * (double)p->L.g.n[2] > (radius == 1 ? 8e5 : 4e5) ? 0 : 2;
     *out = p;
     return STENCIL_OK;
 }
@@ -1130,11 +1257,26 @@ static stencil_status run_args(stencil_plan p, void** fields, int64_t nsteps, co
 
 static stencil_status prepare_points(stencil_plan p, const stencil_source* src, const stencil_receivers* rec) {
     const Variant var = plan_variant(p, p->variant);
+    if (var.march2d) {
+        HostPoints H;
+        const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
+        p->src.n = p->src.ngrp = 0;
+        host_strips(p->L, p->radius, ns, ns ? src->pos : nullptr, H, march_margin(p->radius));
+        ST_TRY(upload_points(H, ns, -1, p->src_ext));
+        host_strips(p->L, p->radius, nr, nr ? rec->pos : nullptr, H, 0);
+        return upload_points(H, nr, -1, p->rec);
+    }
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     ST_TRY(build_points(p->L, src ? src->n : 0, src ? src->pos : nullptr, cfg, p->src));
     if (var.tb) ST_TRY(build_points(p->L, src ? src->n : 0, src ? src->pos : nullptr, var.cfg, p->src_ext, 4));
     ST_TRY(build_points(p->L, rec ? rec->n : 0, rec ? rec->pos : nullptr, -1, p->rec));
     return STENCIL_OK;
+}
+
+// a large 2D wave plan runs several steps per launch if it has a second field pair
+static bool march_wants_pair(const stencil_plan_s* p) {
+    return p->kind == STENCIL_WAVE2 && p->bc == STENCIL_BC_DIRICHLET0 &&
+           march_steps(p->kind, p->dtype, p->radius, p->L) > 1;
 }
 
 // workspace bytes the plan's current variant needs: the second field pair
@@ -1147,6 +1289,7 @@ static size_t run_workspace_bytes(const stencil_plan_s* p) {
         return b;
     }
     const Variant var = plan_variant(p, p->variant);
+    if (var.march2d && march_wants_pair(p)) return 2 * (size_t)round_up(p->L.bytes, 256);
     if (!var.tb) return 0;
     if (p->batch) {
         size_t b = 0;
@@ -1158,6 +1301,7 @@ static size_t run_workspace_bytes(const stencil_plan_s* p) {
 }
 
 static stencil_status check_workspace(const stencil_plan_s* p) {
+    if (plan_variant(p, p->variant).march2d) return STENCIL_OK;   // runs step by step without one
     const size_t need = run_workspace_bytes(p);
     if (need > 0 && (!p->ws || p->ws_bytes < need))
         return fail(STENCIL_E_STATE, "the temporally blocked variant needs a workspace of " + std::to_string(need) +
@@ -1210,6 +1354,8 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)(uintptr_t)(rec ? rec->trace : nullptr),
                                     (int64_t)(uintptr_t)p->src.off.buf.p,
                                     (int64_t)(uintptr_t)p->rec.off.buf.p,
+                                    (int64_t)(uintptr_t)p->rec.zyx4.buf.p,
+                                    (int64_t)(uintptr_t)p->rec.tiles.buf.p,
                                     (int64_t)(uintptr_t)p->src.zyx4.buf.p,
                                     (int64_t)(uintptr_t)p->src.tiles.buf.p,
                                     (int64_t)(uintptr_t)p->src_ext.zyx4.buf.p,
@@ -1217,6 +1363,7 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)(uintptr_t)p->ws,
                                     p->src.n,
                                     p->src.ngrp,
+                                    (int64_t)p->src_ext.dense,
                                     p->src_ext.n,
                                     p->rec.n,
                                     (int64_t)(uintptr_t)p->src.grp.buf.p,
@@ -1266,15 +1413,22 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
     HostPoints hs, he, hr;
-    host_points(L, ns, ns ? src->pos : nullptr, cfg, hs);
-    if (var.tb) host_points(L, ns, ns ? src->pos : nullptr, var.cfg, he, 4);
-    host_points(L, nr, nr ? rec->pos : nullptr, -1, hr);
+    const bool ext = var.tb || var.march2d;   // a second list of sources
+    if (var.march2d) {
+        host_points(L, 0, nullptr, -1, hs);
+        host_strips(L, p->radius, ns, ns ? src->pos : nullptr, he, march_margin(p->radius));
+        host_strips(L, p->radius, nr, nr ? rec->pos : nullptr, hr, 0);
+    } else {
+        host_points(L, ns, ns ? src->pos : nullptr, cfg, hs);
+        if (var.tb) host_points(L, ns, ns ? src->pos : nullptr, var.cfg, he, 4);
+        host_points(L, nr, nr ? rec->pos : nullptr, -1, hr);
+    }
     const bool scaled = ns > 0 && src->scale;
     // the regions this run needs, laid out from offset 0 first to size them
     ScratchCursor sizing{0};
     ScratchPoints ps, pe, pr;
     place_points(sizing, hs, ps);
-    if (var.tb) place_points(sizing, he, pe);
+    if (ext) place_points(sizing, he, pe);
     place_points(sizing, hr, pr);
     if (scaled) sizing.take(sizeof(double) * (size_t)(nsteps * ns));
     if (sizing.used > kNoAllocScratchBytes)
@@ -1286,12 +1440,12 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     ST_TRY(noalloc_scratch(base));
     ScratchCursor cur{(uintptr_t)base};
     place_points(cur, hs, ps);
-    if (var.tb) place_points(cur, he, pe);
+    if (ext) place_points(cur, he, pe);
     place_points(cur, hr, pr);
     double* amounts = scaled ? (double*)cur.take(sizeof(double) * (size_t)(nsteps * ns)) : nullptr;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(fill_points(hs, ps, s));
-    if (var.tb) HIP_TRY(fill_points(he, pe, s));
+    if (ext) HIP_TRY(fill_points(he, pe, s));
     HIP_TRY(fill_points(hr, pr, s));
     const double* amp = ns ? src->amp : nullptr;
     if (scaled) {
@@ -1299,11 +1453,14 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
         amp = amounts;
     }
     RunLists RL;
+    RL.dense = he.dense;
     RL.st = scratch_src_list(hs, ps, amp);
-    RL.se = var.tb ? scratch_src_list(he, pe, amp) : SrcList{};
+    RL.se = ext ? scratch_src_list(he, pe, amp) : SrcList{};
     RL.rl.n = hr.n;
     RL.rl.off = (const int64_t*)pr.off;
     RL.rl.trace = nr ? rec->trace : nullptr;
+    RL.rl.zyx4 = (const int*)pr.zyx4;
+    RL.rl.tile_begin = (const int*)pr.tiles;
     ST_TRY(enqueue_run(p, fields[0], fields[1], p->kind == STENCIL_WAVE2 ? fields[2] : nullptr, nsteps, RL, s));
     if (nsteps & 1) std::swap(fields[0], fields[1]);
     return STENCIL_OK;
@@ -2825,23 +2982,15 @@ static stencil_status time_heat2d_graph(stencil_plan p, int var, const void* in,
     constexpr int kSteps = 96;
     if (!p->cap) HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
     const int T = var == 0 ? 1 : kHeat2dCfgs[var - 1].t;
-    Box3 box{};
-    for (int a = 0; a < 3; a++) {
-        box.lo[a] = 0;
-        box.n[a] = p->L.g.n[a];
-    }
     HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
     const void* src = in;
     void* dst = s0;
     for (int k = 0; k < kSteps / T && e == hipSuccess; k++) {
         if (var == 0) {
-            ZView v{};
-            v.u = src;
-            v.prev = dst;
-            v.out = dst;
-            v.g = p->L.g;
-            e = launch_point(MODE_HEAT, p->radius, p->dtype, v, p->w, box, p->cap);
+            // the whole run by strips (on the scratch fields, whatever they hold)
+            if (k == 0 && enqueue_run_march2d(p, s0, s1, nullptr, kSteps, RunLists{}, p->cap) != STENCIL_OK)
+                e = hipErrorUnknown;
         } else {
             e = launch_heat2d_tb(var - 1, p->radius, (const float*)src, (float*)dst, p->L.g, p->w, p->cap);
         }
