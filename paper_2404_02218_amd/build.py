@@ -26,7 +26,7 @@ COMMON = ["-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE,
 # clauses issues its loads earlier (2% per launch at 512^3, the same bits).
 SOURCE_FLAGS = {"zmarch_tb.hip": ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]}
 SOURCES = ["zmarch_tb.hip", "zmarch_tb_heat.hip", "zmarch_tb_damp.hip", "heat2d_tb.hip", "program.hip", "zmarch_f32.hip", "zmarch_adj.hip", "zmarch_bf16.hip", "zmarch_f16.hip",
-           "kernels.hip", "zbrick.hip", "march2d.hip", "checks.hip", "runtime.cpp", "program_rtc.cpp"]
+           "kernels.hip", "zbrick.hip", "march2d.hip", "step2d.hip", "checks.hip", "runtime.cpp", "program_rtc.cpp"]
 
 
 def _compile(src: str) -> str:
