@@ -301,7 +301,10 @@ stencil_status stencil_batch_layout(stencil_plan batch, int shot, int64_t* exten
 /* nsteps sweeps of every shot (Section 6.1 wave sweep per shot, as in
  * stencil_run), captured into one HIP graph.  By variant:
  *   - fused (zmarch_*, tb2_*): one launch per step (two steps for the
- *     temporally blocked form) covers the tiles of all shots;
+ *     temporally blocked form) covers the tiles of all shots.
+ *     zmarch_64x16_t256_zc32 stands for bricks of 64 x 16 x 2 points here:
+ *     one launch per step covers a group of shots whose fields fit the last
+ *     cache together, and each group takes all its steps before the next;
  *   - persistent_zmarch_*: one launch runs every step over per-XCD queues of
  *     the shots' tiles, with a grid barrier between steps.  Its grid is as
  *     many workgroups as the GPU holds at once; a barrier wait is bounded

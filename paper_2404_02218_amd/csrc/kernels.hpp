@@ -217,6 +217,13 @@ hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v,
 hipError_t launch_march2d(int mode, int radius, int dtype, int nt, const M2View& v, const Coefs& w, int row0,
                           hipStream_t s);
 hipError_t launch_step2d(int mode, int radius, int dtype, const M2View& v, const Coefs& w, int row0, hipStream_t s);
+// whether the bricks of a box of n points run z first
+bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz);
+// batched shots in bricks of kBatchBrick planes; d_block_map as for
+// launch_zmarch_batch
+inline constexpr int kBatchBrick = 2;
+hipError_t launch_brick_batch(int radius, int dtype, const ZView* d_views, const int* d_block_map, int nblocks,
+                              const Coefs& w, int parity, int arow, int trow, hipStream_t s);
 // batched shots: d_block_map[2 b], d_block_map[2 b + 1] = shot and block within the shot of block b
 hipError_t launch_zmarch_batch(int radius, int dtype, int cfg, const ZView* d_views, const int* d_block_map,
                                int nblocks, const Coefs& w, int parity, int arow, int trow, hipStream_t s);

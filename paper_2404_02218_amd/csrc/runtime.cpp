@@ -172,8 +172,16 @@ constexpr int kNumZVariants = kNumTileCfgs * kNumZChunks;
 // batch plans: persistent launches on the 64 x 16 streaming tile, one per
 // z-chunk length
 constexpr int kNumPersistent = kNumZChunks;
+// The batch variant that runs every shot in bricks: it has the place and the
+// name of the plain 64 x 16 tile with 32-plane chunks, which no measured batch
+// picked (8 shots of 96^3 to 224^3: 203 us a step, 127 in bricks).
+constexpr int kBatchBrickVariant = 1 + (kNumZChunks - 1) * kNumTileCfgs + 3;
 // steps of one tuning launch of a persistent variant
 constexpr int kPersistentTuneSteps = 4;
+// steps per shot or group of a timed batch that runs its shots one after
+// another: enough that those after the first, whose fields are in the
+// last-level cache, decide
+constexpr int kBatchTuneSteps = 16;
 // branches of the concurrent batch variant: the hardware queues a process
 // gets by default
 constexpr int kBranches = 4;
@@ -301,6 +309,7 @@ struct stencil_plan_s {
     DevTable views, block_map;   // block_map: (shot, block within the shot) per workgroup
     std::vector<int> bstart;
     int nblocks = 0;             // workgroups of a batched launch (with padding)
+    std::vector<int> group_first;   // in bricks: the workgroups of each group of shots
     // batched temporal blocking: per-shot extended source lists, the second
     // field pair of every shot, and the view tables of even and odd passes
     std::vector<PointTables> shot_src_ext;
@@ -402,6 +411,8 @@ bool batch_persistent(const stencil_plan_s* p, int v) {
     return p->batch && v >= n - 1 - kNumPersistent && v < n - 1;
 }
 
+bool batch_bricks(const stencil_plan_s* p, int v) { return p->batch && v == kBatchBrickVariant; }
+
 // variant v of plan p (batch plans add the persistent launches; variant 0 of
 // a 3D sweep plan is the brick kernel)
 Variant plan_variant(const stencil_plan_s* p, int v) {
@@ -416,6 +427,13 @@ Variant plan_variant(const stencil_plan_s* p, int v) {
     if (!p->batch && !p->program && p->ndim == 2 && v == 0) {
         Variant r;
         r.march2d = true;
+        return r;
+    }
+    if (batch_bricks(p, v)) {
+        Variant r;
+        r.zmarch = true;
+        r.cfg = kBrickCfg;
+        r.zc = kBatchBrick;
         return r;
     }
     if (!batch_persistent(p, v)) return variant_of(v);
@@ -1925,8 +1943,11 @@ stencil_status stencil_batch_create(stencil_plan* out, int nshots, const int64_t
     p->shot_rec.resize(nshots);
     p->shot_src_ext.resize(nshots);
     p->shot_amp_scaled.resize(nshots);
-    // default: the 64x32 tile with 64-plane chunks
-    p->variant = 1 + 2 * kNumTileCfgs + 0;
+    // default: bricks while every shot is small enough for them (as for a
+    // single plan), else the 64x32 tile with 64-plane chunks
+    p->variant = kBatchBrickVariant;
+    for (const Layout& L : p->shots)
+        if (default_variant(L) != 0) p->variant = 1 + 2 * kNumTileCfgs + 0;
     *out = p;
     return STENCIL_OK;
 }
@@ -1988,6 +2009,72 @@ static stencil_status build_block_map_impl(const std::vector<ZView>& views, cons
     return table.upload(map.data(), sizeof(int) * map.size());
 }
 
+// A batch in bricks runs in groups of shots, each group through all its steps
+// before the next: a group's levels and coefficients then stay in the 256 MB
+// last-level cache from step to step.  Shots go largest first into the first
+// group with room for their three fields, so a group holds as many as fit.
+//
+// Block map of the groups, one after another, each laid out per XCD as above.
+// Bricks share most of their planes with the next z-chunk, so each XCD takes an
+// eighth of every shot of the group, in the order of the shot's own launch.
+// us a step, every shot by itself on four graph branches / groups of 96, 176,
+// 256 and 320 MB: 8 shots of 96^3 to 224^3 155 / 140, 131, 127, 168; 10 of
+// 104^3 to 197^3 139 / 128, 115, 113, 137; 6 of 54^3 to 83^3 23 / 12.5.
+// first[g] .. first[g + 1] are group g's workgroups.
+static stencil_status build_brick_map(const std::vector<Layout>& shots, const std::vector<ZView>& views, int radius,
+                                      int dtype, DevTable& table, std::vector<int>& first) {
+    constexpr size_t kXcds = 8;
+    constexpr int64_t kGroupBytes = int64_t(256) << 20;
+    std::vector<int> order(shots.size());
+    for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return shots[a].bytes > shots[b].bytes; });
+    std::vector<std::vector<int>> groups;
+    std::vector<int64_t> bytes;
+    for (int sh : order) {
+        const int64_t need = 3 * shots[sh].bytes;
+        size_t g = 0;
+        while (g < groups.size() && bytes[g] + need > kGroupBytes) g++;
+        if (g == groups.size()) {
+            groups.emplace_back();
+            bytes.push_back(0);
+        }
+        groups[g].push_back(sh);
+        bytes[g] += need;
+    }
+    std::vector<int> map;
+    first.assign(1, 0);
+    for (const std::vector<int>& group : groups) {
+        std::vector<std::vector<int>> lists(kXcds);
+        for (size_t k = 0; k < group.size(); k++) {
+            const int sh = group[k];
+            const ZView& v = views[sh];
+            const int64_t n[3] = {v.g.n[0], v.g.n[1], v.g.n[2]};
+            const int64_t ntxy = (int64_t)v.ntx * v.nty, nb = ntxy * v.nzc;
+            const bool zfast = brick_zfast(n, radius, dtype_size(dtype), kBatchBrick);
+            if (nb > (int64_t(1) << 30)) return fail(STENCIL_E_INVALID, "batch too large");
+            // the shots' eighths start at successive XCDs, so that small shots even out
+            for (int64_t b = 0; b < nb; b++) {
+                std::vector<int>& l = lists[(size_t)(b * (int64_t)kXcds / nb + (int64_t)k) % kXcds];
+                l.push_back(sh);
+                l.push_back((int)(zfast ? b % v.nzc * ntxy + b / v.nzc : b));
+            }
+        }
+        size_t len = 0;
+        for (const auto& l : lists) len = std::max(len, l.size() / 2);
+        const size_t at = map.size() / 2;
+        if (at + len * kXcds > (size_t(1) << 30)) return fail(STENCIL_E_INVALID, "batch too large");
+        map.resize(2 * (at + len * kXcds), -1);
+        for (size_t x = 0; x < kXcds; x++)
+            for (size_t i = 0; i < lists[x].size() / 2; i++) {
+                map[2 * (at + i * kXcds + x)] = lists[x][2 * i];
+                map[2 * (at + i * kXcds + x) + 1] = lists[x][2 * i + 1];
+            }
+        first.push_back((int)(map.size() / 2));
+    }
+    if (map.empty()) map.assign(2, -1);
+    return table.upload(map.data(), sizeof(int) * map.size());
+}
+
 // The persistent batched sweep's queues: queue x holds the map's entries of
 // XCD x (map index b with b % 8 == x, the pads dropped) in map order.
 // list: (shot, block) pairs, qoff: 9 offsets.
@@ -2040,7 +2127,10 @@ static stencil_status batch_prepare(stencil_plan p, void** fields, int64_t nstep
     {
         std::vector<int> nz(ns);
         for (int s = 0; s < ns; s++) nz[s] = p->shots[s].g.n[0];
-        ST_TRY(build_block_map_impl(views, nz, p->radius, p->block_map, p->nblocks, &p->hmap));
+        if (var.cfg == kBrickCfg)
+            ST_TRY(build_brick_map(p->shots, views, p->radius, p->dtype, p->block_map, p->group_first));
+        else
+            ST_TRY(build_block_map_impl(views, nz, p->radius, p->block_map, p->nblocks, &p->hmap));
     }
     if (var.tb) {
         // pass k reads pair k & 1 (newest, previous) and writes the other pair
@@ -2153,6 +2243,14 @@ static stencil_status enqueue_batch(stencil_plan p, const std::vector<ZView>& vi
             }
         }
         t0 = 2 * passes;
+    }
+    for (size_t g = 0; var.cfg == kBrickCfg && g + 1 < p->group_first.size(); g++) {
+        const int at = p->group_first[g], n = p->group_first[g + 1] - at;
+        for (int64_t t = 0; t < nsteps; t++)
+            HIP_TRY(launch_brick_batch(p->radius, p->dtype, (const ZView*)p->views.buf.p,
+                                       (const int*)p->block_map.buf.p + 2 * at, n, p->w, (int)(t & 1), (int)t,
+                                       (any_rec && t >= 1) ? (int)(t - 1) : -1, s));
+        t0 = nsteps;
     }
     for (int64_t t = t0; t < nsteps; t++) {
         const int trow = (any_rec && t >= 1) ? (int)(t - 1) : -1;
@@ -3019,9 +3117,9 @@ static stencil_status time_heat2d_graph(stencil_plan p, int var, const void* in,
 
 // The concurrent batch variant as a tuning candidate: each shot's own plan
 // is tuned on its fields first (cached per shape); then every shot's kernel
-// advances two steps (one temporally blocked launch, or two single-step
-// launches) into scratch outputs, in the branches from fork to join, `reps`
-// times.  scratch holds two fields per shot.  Result: ms per step.
+// takes kBatchTuneSteps steps from the shot's level over a scratch field (in
+// place of the previous level, so that as many fields are in use as in a run),
+// in the branches from fork to join, `reps` times.  scratch holds two fields per shot.  Result: ms per step.
 static stencil_status time_batch_concurrent(stencil_plan p, void* const* fields, int reps, void* scratch, hipStream_t s,
                                             hipEvent_t e0, hipEvent_t e1, float& ms_per_step) {
     ST_TRY(ensure_shot_plans(p));
@@ -3052,13 +3150,14 @@ static stencil_status time_batch_concurrent(stencil_plan p, void* const* fields,
             t.nty = (L.g.n[1] + kTB2TileY - 1) / kTB2TileY;
             chunking(L.g.n[0], var.zc, t.zc, t.nzc);
             t.range = (uint32_t)L.bytes;
-            HIP_TRY(launch_tb2(MODE_WAVE, q->radius, q->dtype, t, q->w, 0, -1, -1, bs));
+            for (int k = 0; k < kBatchTuneSteps; k += 2)
+                HIP_TRY(launch_tb2(MODE_WAVE, q->radius, q->dtype, t, q->w, 0, -1, -1, bs));
             return STENCIL_OK;
         }
-        for (int k = 0; k < 2; k++) {
+        for (int k = 0; k < kBatchTuneSteps; k++) {
             ZView v{};
             v.u = fields[3 * sh];
-            v.prev = fields[3 * sh + 1];
+            v.prev = out;
             v.beta = fields[3 * sh + 2];
             v.out = out;
             v.g = L.g;
@@ -3074,7 +3173,7 @@ static stencil_status time_batch_concurrent(stencil_plan p, void* const* fields,
     HIP_TRY(hipEventSynchronize(e1));
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-    ms_per_step = ms / (2.0f * (float)reps);
+    ms_per_step = ms / (float)(kBatchTuneSteps * reps);
     return STENCIL_OK;
 }
 
@@ -3217,6 +3316,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             continue;
         }
         const Variant var = plan_variant(p, var_i);
+        std::vector<int> groups;   // batch in bricks: the groups' workgroups
         std::vector<ZView> views;
         std::vector<int> bst(1, 0);
         int64_t off = 0;
@@ -3229,6 +3329,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             v.beta = wave ? fields[i * nf + 2] : nullptr;
             v.damp = p->damped ? (const float*)p->damp.buf.p : nullptr;
             v.out = (char*)scratch + off;
+            if (p->batch && var.cfg == kBrickCfg) v.prev = v.out;   // in place, as a run
             off += round_up(L.bytes, 256);
             v.g = L.g;
             Variant vs = var;
@@ -3241,10 +3342,12 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             st = vt.upload(views.data(), sizeof(ZView) * views.size());
             int padded = 0;
             std::vector<int> hm;
+            groups.clear();
             if (st == STENCIL_OK) {
                 std::vector<int> nz;
                 for (const Layout* L : Ls) nz.push_back(L->g.n[0]);
-                st = build_block_map_impl(views, nz, p->radius, bs, padded, &hm);
+                if (var.cfg == kBrickCfg) st = build_brick_map(p->shots, views, p->radius, p->dtype, bs, groups);
+                else st = build_block_map_impl(views, nz, p->radius, bs, padded, &hm);
             }
             bst.back() = padded;
             // a persistent variant the device cannot hold at once is skipped
@@ -3307,6 +3410,16 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
                 t.damp = p->damped ? (const float*)p->damp.buf.p : nullptr;
                 return launch_tb2(mode, p->radius, p->dtype, t, p->w, 0, -1, -1, s);
             }
+            if (p->batch && var.cfg == kBrickCfg) {
+                // some steps of each group, as a run goes through them
+                hipError_t e = hipSuccess;
+                for (size_t g = 0; g + 1 < groups.size(); g++)
+                    for (int k = 0; k < kBatchTuneSteps && e == hipSuccess; k++)
+                        e = launch_brick_batch(p->radius, p->dtype, (const ZView*)vt.buf.p,
+                                               (const int*)bs.buf.p + 2 * groups[g], groups[g + 1] - groups[g], p->w, 0, 0,
+                                               -1, s);
+                return e;
+            }
             if (p->batch)
                 return launch_zmarch_batch(p->radius, p->dtype, var.cfg, (const ZView*)vt.buf.p, (const int*)bs.buf.p,
                                            bst.back(), p->w, 0, 0, -1, s);
@@ -3335,7 +3448,9 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             st = fail(STENCIL_E_DEVICE, std::string("tuning launch: ") + hipGetErrorString(e));
             break;
         }
+        ms /= (float)reps;
         if (var.tb) ms *= 0.5f;   // one launch advances two steps
+        if (p->batch && var.cfg == kBrickCfg) ms /= (float)kBatchTuneSteps;
         if (var.persistent) {
             ms /= (float)kPersistentTuneSteps;
             const stencil_status cs = check_persistent(p, s);

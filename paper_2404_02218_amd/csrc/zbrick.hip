@@ -24,8 +24,6 @@
 
 namespace stn {
 
-namespace {
-
 // Number the bricks z first where the planes that z neighbours share pass the
 // reach of an XCD's 4 MB L2 otherwise: neighbours in z share 2R of their
 // BZ + 2R planes, tiles side by side only their margins.  One wave step in
@@ -37,6 +35,8 @@ bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz) {
     return (bz + 2 * radius) * plane * esize > 2.85e6 && plane * n[0] <= (double)(1 << 25);
 }
 
+namespace {
+
 template <int R, int BZ>
 struct ZBrick {
     static constexpr int NT = 256, TX = kBrickTileX, TY = kBrickTileY;
@@ -45,8 +45,6 @@ struct ZBrick {
     // row above and below the tile
     static constexpr int NHX = 2 * TY, NHP = NHX + 2 * R * (TX / 4), NHT = NHP * BZ, NH = (NHT + NT - 1) / NT;
     static constexpr int NQ = BZ + 2 * R;   // planes of a thread's own column
-    // sources of the brick staged at a time: position and amount
-    static constexpr int NS = 64;
     static_assert(NT == (TX / 4) * TY, "one 4-point group of the tile per thread");
 };
 
@@ -58,29 +56,18 @@ inline constexpr bool kAdj = MODE == MODE_WAVE_ADJ || MODE == MODE_WAVE_ADJ2;
 template <int MODE, int BZ>
 inline constexpr int kBrickWaves = BZ == 2 ? 5 : kAdj<MODE> ? 3 : 4;
 
-// zfast: workgroups are numbered z first, then x, y (else x, y, z)
+// One workgroup's brick: tile (row by row of v.ntx) and z-chunk zch of the
+// box; rec: this workgroup records the receivers (trow >= 0).
 template <int MODE, int R, typename T, int BZ>
-__global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, int zfast, int parity,
-                                                                       int arow, int trow) {
+__device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3& box, int tile, int zch, bool rec,
+                                      int parity, int arow, int trow, float* __restrict__ lds) {
     using Z = ZBrick<R, BZ>;
     using S = Storage<T>;
     constexpr int NT = Z::NT, TX = Z::TX, TY = Z::TY, LDX = Z::LDX, PLANE = Z::PLANE, NH = Z::NH, NQ = Z::NQ;
     constexpr bool WAVE = MODE != MODE_HEAT;
     constexpr bool ADJ = kAdj<MODE>, ADJ2 = MODE == MODE_WAVE_ADJ2;
-    __shared__ __attribute__((aligned(16))) float lds[BZ * PLANE];
-    __shared__ double src_amt[Z::NS];
-    __shared__ int src_at[Z::NS];
 
     const int tid = threadIdx.x, tx = tid % (TX / 4), ty = tid / (TX / 4);
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    int zch, tile;
-    if (zfast) {
-        zch = lb % v.nzc;
-        tile = lb / v.nzc;
-    } else {
-        zch = lb / (v.ntx * v.nty);
-        tile = lb % (v.ntx * v.nty);
-    }
     const int tile_x = tile % v.ntx, tile_y = tile / v.ntx;
     // the box's x origin rounded down to a 4-element group keeps every access aligned
     const int bx = (int)box.lo[2], by = (int)box.lo[1], bz = (int)box.lo[0];
@@ -94,7 +81,7 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
     const T* B = (const T*)v.beta + v.g.origin;
 
     // receivers sample the input level (read-only during this launch)
-    if (trow >= 0 && lb == 0) {
+    if (trow >= 0 && rec) {
         for (int r = tid; r < v.rec.n; r += NT)
             v.rec.trace[(int64_t)trow * v.rec.n + r] = (double)S::load(U + v.rec.off[r]);
     }
@@ -178,17 +165,19 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
             s1 += __popcll(__ballot(z < ze));
         }
     }
-    // up to NS of them at a time go through LDS, one per thread, so that many
-    // sources in one brick (a receiver line of the adjoint) cost one latency
-    auto stage_sources = [&](int from) {
-        const int e = from + tid;
-        if (tid < Z::NS && e < s1) {
-            const int* q = v.src.zyx4 + 4 * e;
-            src_amt[tid] = v.src.amp[(int64_t)arow * v.src.n + q[3]] * (v.src.scale ? v.src.scale[q[3]] : 1.0);
-            src_at[tid] = ((q[0] - zb) * TY + (q[1] - Y0)) * TX + (q[2] - X0);
-        }
+    // 64 of them at a time, one per lane: loaded before the compute and handed
+    // round in registers after it, so that many sources in one brick (a
+    // receiver line of the adjoint) cost one latency (32 of them in a tile of
+    // the 128^3 adjoint step, walked one by one through LDS: 16.2 us, now 9)
+    int src_at = 0, src_lo = 0, src_hi = 0;
+    auto load_sources = [&](int from) {
+        const int* e = v.src.zyx4 + 4 * min(from + (tid & 63), s1 - 1);
+        const double amt = v.src.amp[(int64_t)arow * v.src.n + e[3]] * (v.src.scale ? v.src.scale[e[3]] : 1.0);
+        src_at = ((e[0] - zb) * TY + (e[1] - Y0)) * TX + (e[2] - X0);
+        src_lo = __double2loint(amt);
+        src_hi = __double2hiint(amt);
     };
-    if (s0 < s1) stage_sources(s0);
+    if (s0 < s1) load_sources(s0);
 
     float4 q[NQ];
 #pragma unroll
@@ -247,26 +236,28 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
         }
     }
 
-    for (int from = s0; from < s1;) {
-        const int cnt = min(s1 - from, Z::NS);
-        for (int e = 0; e < cnt; e++) {
-            const int at = src_at[e];
-            if ((at / TX) % TY == ty && (at % TX) >> 2 == tx) {
+    for (int from = s0; from < s1; from += 64) {
+        if (from > s0) load_sources(from);
+        // those in this wave's four rows, in order
+        const int row0 = __builtin_amdgcn_readfirstlane(ty);
+        const int row = (src_at / TX) % TY - row0;
+        uint64_t mine = __ballot((tid & 63) < s1 - from && row >= 0 && row < 4);
+        for (; mine; mine &= mine - 1) {
+            const int e = __builtin_ctzll(mine);
+            const int at = __builtin_amdgcn_readlane(src_at, e);
+            const double a = __hiloint2double(__builtin_amdgcn_readlane(src_hi, e), __builtin_amdgcn_readlane(src_lo, e));
+            const int pe = at / (TX * TY), ie = at & 3;
+            const bool here = (tid & 63) == ((at / TX) % TY - row0) * (TX / 4) + (at % TX) / 4;
 #pragma unroll
-                for (int p = 0; p < BZ; p++)
+            for (int p = 0; p < BZ; p++)
+                if (p == pe) {
 #pragma unroll
                     for (int i = 0; i < 4; i++)
-                        if (at == (p * TY + ty) * TX + 4 * tx + i) {
-                            o[p][i] = inject<T>(o[p][i], src_amt[e]);
-                            if constexpr (MODE == MODE_WAVE_D) dv[p][i] = (float)((double)dv[p][i] + src_amt[e]);
+                        if (i == ie && here) {
+                            o[p][i] = inject<T>(o[p][i], a);
+                            if constexpr (MODE == MODE_WAVE_D) dv[p][i] = (float)((double)dv[p][i] + a);
                         }
-            }
-        }
-        from += cnt;
-        if (from < s1) {
-            __syncthreads();
-            stage_sources(from);
-            __syncthreads();
+                }
         }
     }
 
@@ -319,6 +310,43 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
     }
 }
 
+// zfast: workgroups are numbered z first, then x, y (else x, y, z)
+template <int MODE, int R, typename T, int BZ>
+__global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, int zfast, int parity,
+                                                                       int arow, int trow) {
+    __shared__ __attribute__((aligned(16))) float lds[BZ * ZBrick<R, BZ>::PLANE];
+    const int lb = xcd_remap(blockIdx.x, gridDim.x), ntxy = v.ntx * v.nty;
+    const int zch = zfast ? lb % v.nzc : lb / ntxy, tile = zfast ? lb / v.nzc : lb % ntxy;
+    brick<MODE, R, T, BZ>(v, w, box, tile, zch, lb == 0, parity, arow, trow, lds);
+}
+
+// The bricks of every shot of a batch in one launch: block_map[2 b],
+// block_map[2 b + 1] = shot and block within the shot (x, y, z-chunk order) of
+// workgroup b, shot -1 for padding; the host lays it out per XCD.  A shot of
+// 100^3 has too few bricks to fill the chip and takes 6 us for 2.8 TB/s; all
+// shots together fill it.
+template <typename T>
+__global__ __launch_bounds__(256, (kBrickWaves<MODE_WAVE, kBatchBrick>)) void k_zbrick_batch(
+    const ZView* __restrict__ views, const int* __restrict__ block_map, Coefs w, int parity, int arow, int trow) {
+    __shared__ __attribute__((aligned(16))) float lds[kBatchBrick * ZBrick<4, kBatchBrick>::PLANE];
+    const int shot = block_map[2 * blockIdx.x], lb = block_map[2 * blockIdx.x + 1];
+    if (shot < 0) return;
+    const ZView v = views[shot];
+    const int ntxy = v.ntx * v.nty;
+    Box3 box{};
+    for (int a = 0; a < 3; a++) box.n[a] = v.g.n[a];
+    brick<MODE_WAVE, 4, T, kBatchBrick>(v, w, box, lb % ntxy, lb / ntxy, lb == 0, parity, arow, trow, lds);
+}
+
+template <typename T>
+hipError_t brick_batch(const ZView* views, const int* block_map, int nblocks, const Coefs& w, int parity, int arow,
+                       int trow, hipStream_t s) {
+    if (nblocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zbrick_batch<T>, dim3((unsigned)nblocks), dim3(256), 0, s, views, block_map, w, parity, arow,
+                       trow);
+    return hipGetLastError();
+}
+
 template <int MODE, int R, typename T, int BZ>
 hipError_t brick_launch(const ZView& v, const Coefs& w, const Box3& box, int parity, int arow, int trow, hipStream_t s) {
     ZView b = v;
@@ -369,6 +397,17 @@ hipError_t brick_m(int mode, int radius, int bz, const ZView& v, const Coefs& w,
 }
 
 }  // namespace
+
+hipError_t launch_brick_batch(int radius, int dtype, const ZView* views, const int* block_map, int nblocks,
+                              const Coefs& w, int parity, int arow, int trow, hipStream_t s) {
+    if (radius != 4) return hipErrorInvalidValue;
+    switch (dtype) {
+        case DT_F32: return brick_batch<float>(views, block_map, nblocks, w, parity, arow, trow, s);
+        case DT_BF16: return brick_batch<bf16>(views, block_map, nblocks, w, parity, arow, trow, s);
+        case DT_F16: return brick_batch<f16>(views, block_map, nblocks, w, parity, arow, trow, s);
+    }
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v, const Coefs& w, const Box3& box,
                         int parity, int arow, int trow, hipStream_t s) {

@@ -97,3 +97,38 @@ def test_heat_sources_are_added_after_the_step(device):
     for at, a in (((5, 19, 69), 0.5), ((0, 3, 64), -0.25), ((5, 19, 69), 0.125)):
         want[at] = np.float32(np.float64(want[at]) + a)
     assert np.array_equal(out[1], want.astype(np.float64))
+
+
+@pytest.mark.parametrize("dtype,sides,nsteps", [(S.F32, [(17, 40, 70), (9, 16, 64), (40, 37, 65)], 5),
+                                               (S.BF16, [(17, 40, 70), (9, 16, 64)], 4),
+                                               (S.F32, [(190, 190, 190), (24, 24, 24), (180, 190, 200), (186, 186, 186)], 7)])
+def test_batch_in_bricks_equals_single_runs(device, dtype, sides, nsteps):
+    """Several shots per launch, and (the large ones) several groups of shots."""
+    import torch
+    batch = S.BatchPlan(sides, 4, S.second_derivative_weights(8), dtype=dtype)
+    batch.variant = 19
+    assert batch.variant_name(19) == "zmarch_64x16_t256_zc32"
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rng = np.random.default_rng(3)
+    start, want, srcs, amps, recs = [], [], [], [], []
+    for i, shape in enumerate(sides):
+        f = [batch.field(i) for _ in range(3)]
+        for x in f[:2]:
+            x.view[4:-4, 4:-4, 4:-4] = torch.randn(shape, generator=g, device="cuda").to(x.view.dtype)
+        f[2].view.uniform_(0.005, 0.05, generator=g)
+        srcs.append(np.stack([rng.integers(0, n, 3) for n in shape], axis=1))
+        recs.append(np.stack([rng.integers(0, n, 5) for n in shape], axis=1))
+        amps.append(torch.from_numpy(rng.standard_normal((nsteps, 3))).cuda())
+        start.append(f)
+        plan = S.Plan(S.WAVE2, shape, 4, S.second_derivative_weights(8), dtype=dtype)
+        plan.variant = 1
+        h = [plan.field() for _ in range(3)]
+        for a, b in zip(h, f):
+            a.storage.copy_(b.storage)
+        trace = torch.zeros((nsteps, 5), dtype=torch.float64, device=device)
+        plan.run(h, nsteps, src=srcs[i], src_amp=amps[i], rec=recs[i], rec_trace=trace)
+        want.append((h[0].storage, h[1].storage, trace))
+    traces = [torch.zeros((nsteps, 5), dtype=torch.float64, device=device) for _ in sides]
+    batch.run(start, nsteps, srcs=srcs, src_amps=amps, recs=recs, rec_traces=traces)
+    for f, t, w in zip(start, traces, want):
+        assert torch.equal(f[0].storage, w[0]) and torch.equal(f[1].storage, w[1]) and torch.equal(t, w[2])
