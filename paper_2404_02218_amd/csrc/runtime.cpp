@@ -878,33 +878,21 @@ stencil_status enqueue_run_tb(stencil_plan p, const Variant& var, void* a, void*
     return STENCIL_OK;
 }
 
-// 2D heat with the multi-step kernel: an even number of T-step passes
-// between the two buffers (so, as after nsteps plain sweeps, the newest level
-// is in a when nsteps is even), then plain sweeps for the rest.
+// 2D heat with the multi-step kernel: as few passes between the two buffers as
+// the kernel's depth allows, odd in number when nsteps is (the newest level
+// then lands where nsteps plain sweeps would leave it), of nearly equal steps.
 static stencil_status enqueue_run_heat2d(stencil_plan p, void* a, void* b, int64_t nsteps, hipStream_t s) {
-    const Layout& L = p->L;
     const int cfg = p->variant - 1;
-    const int T = kHeat2dCfgs[cfg].t;
-    int64_t passes = nsteps / T;
-    if (passes & 1) passes--;
+    const int64_t T = kHeat2dCfgs[cfg].t;
+    int64_t passes = (nsteps + T - 1) / T;
+    if ((passes ^ nsteps) & 1) passes++;
     void* cur = a;
     void* nxt = b;
     for (int64_t k = 0; k < passes; k++) {
-        HIP_TRY(launch_heat2d_tb(cfg, p->radius, (const float*)cur, (float*)nxt, L.g, p->w, s));
-        std::swap(cur, nxt);
-    }
-    Box3 box{};
-    for (int a3 = 0; a3 < 3; a3++) {
-        box.lo[a3] = 0;
-        box.n[a3] = L.g.n[a3];
-    }
-    for (int64_t t = passes * T; t < nsteps; t++) {
-        ZView v{};
-        v.u = cur;
-        v.prev = nxt;
-        v.out = nxt;
-        v.g = L.g;
-        HIP_TRY(launch_point(MODE_HEAT, p->radius, p->dtype, v, p->w, box, s));
+        const int64_t t0 = nsteps * k / passes, t1 = nsteps * (k + 1) / passes;
+        const float* const h0 = (const float*)((t0 & 1) ? b : a);   // even levels have a's halo, odd ones b's
+        const float* const h1 = (const float*)((t0 & 1) ? a : b);
+        HIP_TRY(launch_heat2d_tb(cfg, p->radius, (const float*)cur, (float*)nxt, h0, h1, p->L.g, p->w, (int)(t1 - t0), s));
         std::swap(cur, nxt);
     }
     return STENCIL_OK;
@@ -1176,10 +1164,14 @@ stencil_status stencil_create(stencil_plan* out, stencil_kind kind, int ndim, co
         return st;
     }
     p->variant = default_variant(p->L);
-    // 2D heat: 8 steps per launch on 16 x 16 tiles in LDS, until the sweep by
-    // strips passes it (us a step, tiles / strips: r = 1 700^2 2.3 / 2.8, 1000^2
-    // 3.7 / 3.4, 2048^2 13 / 5.0; r = 2 512^2 2.0 / 2.9, 700^2 3.4 / 3.0)
-    if (heat2d_supported(p)) p->variant = p->L.g.n[1] * (double)p->L.g.n[2] > (radius == 1 ? 8e5 : 4e5) ? 0 : 2;
+    // 2D heat: 8 steps per launch on 16 x 16 tiles, on larger grids 16 (r = 1) or
+    // 8 (r = 2) on 32 x 32 tiles, then the sweep by strips (us a step, r = 1: 256^2
+    // 0.61, 0.68, 2.2; 512^2 1.1, 0.72, 2.3; 1400^2 -, 3.1, 3.7; 2048^2 13, 6, 5.0;
+    // r = 2: 256^2 0.95, 1.05, 2.3; 512^2 2.1, 1.1, 2.5; 1400^2 -, 5.0, 4.6)
+    if (heat2d_supported(p)) {
+        const double pts = p->L.g.n[1] * (double)p->L.g.n[2];
+        p->variant = pts <= 1.2e5 ? 2 : pts <= (radius == 1 ? 2.5e6 : 1.5e6) ? (radius == 1 ? 4 : 3) : 0;
+    }
     *out = p;
     return STENCIL_OK;
 }
@@ -3090,7 +3082,8 @@ static stencil_status time_heat2d_graph(stencil_plan p, int var, const void* in,
             if (k == 0 && enqueue_run_march2d(p, s0, s1, nullptr, kSteps, RunLists{}, p->cap) != STENCIL_OK)
                 e = hipErrorUnknown;
         } else {
-            e = launch_heat2d_tb(var - 1, p->radius, (const float*)src, (float*)dst, p->L.g, p->w, p->cap);
+            e = launch_heat2d_tb(var - 1, p->radius, (const float*)src, (float*)dst, (const float*)in, (const float*)in, p->L.g,
+                                 p->w, T, p->cap);
         }
         src = dst;
         dst = dst == s0 ? s1 : s0;
@@ -3377,11 +3370,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             }
             if (st != STENCIL_OK) break;
         }
-        const bool heat2d = p->ndim == 2 && var_i > 0;
         auto launch = [&]() -> hipError_t {
-            if (heat2d)
-                return launch_heat2d_tb(var_i - 1, p->radius, (const float*)views[0].u, (float*)views[0].out, p->L.g,
-                                        p->w, s);
             if (var.tb && p->batch)
                 return tb2_batch(p->dtype, (const TBView*)tvt.buf.p, (const int*)bs.buf.p, bst.back(), p->w, 0, -1, -1, s);
             if (var.persistent) {
@@ -3459,7 +3448,6 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
                 break;
             }
         }
-        if (heat2d) ms /= (float)kHeat2dCfgs[var_i - 1].t;
         if (ms < best_ms) {
             best_ms = ms;
             best = var_i;

@@ -125,3 +125,21 @@ def test_damped_passes_equal_single_steps(device, radius, shape):
     for _ in range(16):
         plan.run(b, 1)
     assert torch.equal(_bits(a[0]), _bits(b[0])) and torch.equal(_bits(a[1]), _bits(b[1]))
+
+
+@pytest.mark.parametrize("radius,shape", [(1, (50, 77)), (1, (100, 3)), (2, (33, 130)), (2, (70, 45))])
+@pytest.mark.parametrize("halo_values", [False, True])
+def test_multistep_heat_keeps_the_halo(device, radius, shape, halo_values):
+    """The multi-step tiles against the sweep by strips, with any halo and any number of steps."""
+    import torch
+    plan = S.Plan(S.HEAT, shape, radius, _weights(S.HEAT, radius))
+    for nsteps in (1, 2, 7, 15, 40):
+        plan.variant = 0
+        want = _fields(plan, 6, halo_values)
+        plan.run(want, nsteps)
+        for v in range(1, plan.variant_count()):
+            plan.variant = v
+            f = _fields(plan, 6, halo_values)
+            plan.run(f, nsteps)
+            r = plan.halo
+            assert torch.equal(f[0].view[r:-r, r:-r], want[0].view[r:-r, r:-r]), (plan.variant_name(v), nsteps)
