@@ -100,10 +100,6 @@ __global__ void k_record(const T* base, RecList rec, int trow) {
 // 16-byte aligned on both sides (the usual case: faces across x and y start
 // at the aligned interior origin), else 1.  Unit -> (row, column) and
 // row -> (z, y) use 32-bit division by precomputed multipliers.
-struct FastDiv {
-    uint32_t m, s, one;   // q = one ? n : (t + ((n - t) >> 1)) >> s, t = mulhi(n, m)
-};
-
 constexpr int kCopyBoxes = 8;
 struct CopyBox {
     int64_t src, dst;      // field element offsets of the box's first source / destination element
@@ -116,25 +112,6 @@ struct CopyPlan {
     uint32_t bstart[kCopyBoxes + 1];   // first workgroup of each box
     CopyBox box[kCopyBoxes];
 };
-
-static FastDiv fast_div(uint32_t d) {
-    FastDiv f{0, 0, 0};
-    if (d <= 1) {
-        f.one = 1;
-        return f;
-    }
-    uint32_t l = 0;
-    while ((uint64_t(1) << l) < d) l++;
-    f.m = (uint32_t)(((uint64_t(1) << 32) * ((uint64_t(1) << l) - d)) / d + 1);
-    f.s = l - 1;
-    return f;
-}
-
-__device__ static inline uint32_t fdiv(uint32_t n, const FastDiv& f) {
-    if (f.one) return n;
-    const uint32_t t = __umulhi(n, f.m);
-    return (t + ((n - t) >> 1)) >> f.s;
-}
 
 template <typename T> struct Vec4;
 template <> struct Vec4<uint32_t> { using type = uint4; };

@@ -18,6 +18,29 @@ enum DType : int { DT_F32 = 0, DT_BF16 = 1, DT_F16 = 2 };
 
 inline int dtype_size(int dt) { return dt == DT_F32 ? 4 : 2; }
 
+// Division of an index below 2^31 by a divisor fixed at launch: a multiply and
+// shifts instead of the thirty instructions of a 32-bit division.
+struct FastDiv {
+    uint32_t d, m, s, one;   // q = one ? n : (t + ((n - t) >> 1)) >> s, t = mulhi(n, m)
+};
+inline FastDiv fast_div(uint32_t d) {
+    FastDiv f{d, 0, 0, 0};
+    if (d <= 1) {
+        f.one = 1;
+        return f;
+    }
+    uint32_t l = 0;
+    while ((uint64_t(1) << l) < d) l++;
+    f.m = (uint32_t)(((uint64_t(1) << 32) * ((uint64_t(1) << l) - d)) / d + 1);
+    f.s = l - 1;
+    return f;
+}
+__device__ static inline uint32_t fdiv(uint32_t n, const FastDiv& f) {
+    if (f.one) return n;
+    const uint32_t t = __umulhi(n, f.m);
+    return (t + ((n - t) >> 1)) >> f.s;
+}
+
 // Padded field layout shared by every field of a plan.  Internal axes are
 // (z, y, x); inactive leading axes of 1D/2D plans have extent 1 and stride 0.
 struct Grid3 {
@@ -219,8 +242,9 @@ hipError_t launch_march2d(int mode, int radius, int dtype, int nt, const M2View&
 hipError_t launch_step2d(int mode, int radius, int dtype, const M2View& v, const Coefs& w, int row0, hipStream_t s);
 // whether the bricks of a box of n points run z first
 bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz);
-// batched shots in bricks of kBatchBrick planes; d_block_map as for
-// launch_zmarch_batch
+// batched shots in bricks of kBatchBrick planes; d_block_map: (shot, tile x, tile
+// y, z-chunk) of every workgroup, tile x -1 for the one that records the
+// shot's receivers, shot -1 for padding
 inline constexpr int kBatchBrick = 2;
 hipError_t launch_brick_batch(int radius, int dtype, const ZView* d_views, const int* d_block_map, int nblocks,
                               const Coefs& w, int parity, int arow, int trow, hipStream_t s);

@@ -2044,26 +2044,27 @@ static stencil_status build_brick_map(const std::vector<Layout>& shots, const st
             const int64_t ntxy = (int64_t)v.ntx * v.nty, nb = ntxy * v.nzc;
             const bool zfast = brick_zfast(n, radius, dtype_size(dtype), kBatchBrick);
             if (nb > (int64_t(1) << 30)) return fail(STENCIL_E_INVALID, "batch too large");
+            auto add = [&](size_t x, int tx, int ty, int zch) {
+                const int e[4] = {sh, tx, ty, zch};
+                lists[x % kXcds].insert(lists[x % kXcds].end(), e, e + 4);
+            };
             // the shots' eighths start at successive XCDs, so that small shots even out
             for (int64_t b = 0; b < nb; b++) {
-                std::vector<int>& l = lists[(size_t)(b * (int64_t)kXcds / nb + (int64_t)k) % kXcds];
-                l.push_back(sh);
-                l.push_back((int)(zfast ? b % v.nzc * ntxy + b / v.nzc : b));
+                const int64_t tile = zfast ? b / v.nzc : b % ntxy, zch = zfast ? b % v.nzc : b / ntxy;
+                add((size_t)(b * (int64_t)kXcds / nb) + k, (int)(tile % v.ntx), (int)(tile / v.ntx), (int)zch);
             }
         }
         size_t len = 0;
-        for (const auto& l : lists) len = std::max(len, l.size() / 2);
-        const size_t at = map.size() / 2;
+        for (const auto& l : lists) len = std::max(len, l.size() / 4);
+        const size_t at = map.size() / 4;
         if (at + len * kXcds > (size_t(1) << 30)) return fail(STENCIL_E_INVALID, "batch too large");
-        map.resize(2 * (at + len * kXcds), -1);
+        map.resize(4 * (at + len * kXcds), -1);
         for (size_t x = 0; x < kXcds; x++)
-            for (size_t i = 0; i < lists[x].size() / 2; i++) {
-                map[2 * (at + i * kXcds + x)] = lists[x][2 * i];
-                map[2 * (at + i * kXcds + x) + 1] = lists[x][2 * i + 1];
-            }
-        first.push_back((int)(map.size() / 2));
+            for (size_t i = 0; i < lists[x].size() / 4; i++)
+                std::copy_n(&lists[x][4 * i], 4, &map[4 * (at + i * kXcds + x)]);
+        first.push_back((int)(map.size() / 4));
     }
-    if (map.empty()) map.assign(2, -1);
+    if (map.empty()) map.assign(4, -1);
     return table.upload(map.data(), sizeof(int) * map.size());
 }
 
@@ -2240,7 +2241,7 @@ static stencil_status enqueue_batch(stencil_plan p, const std::vector<ZView>& vi
         const int at = p->group_first[g], n = p->group_first[g + 1] - at;
         for (int64_t t = 0; t < nsteps; t++)
             HIP_TRY(launch_brick_batch(p->radius, p->dtype, (const ZView*)p->views.buf.p,
-                                       (const int*)p->block_map.buf.p + 2 * at, n, p->w, (int)(t & 1), (int)t,
+                                       (const int*)p->block_map.buf.p + 4 * (size_t)at, n, p->w, (int)(t & 1), (int)t,
                                        (any_rec && t >= 1) ? (int)(t - 1) : -1, s));
         t0 = nsteps;
     }
@@ -3405,7 +3406,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
                 for (size_t g = 0; g + 1 < groups.size(); g++)
                     for (int k = 0; k < kBatchTuneSteps && e == hipSuccess; k++)
                         e = launch_brick_batch(p->radius, p->dtype, (const ZView*)vt.buf.p,
-                                               (const int*)bs.buf.p + 2 * groups[g], groups[g + 1] - groups[g], p->w, 0, 0,
+                                               (const int*)bs.buf.p + 4 * (size_t)groups[g], groups[g + 1] - groups[g], p->w, 0, 0,
                                                -1, s);
                 return e;
             }

@@ -43,9 +43,9 @@ struct ZBrick {
     static constexpr int LDX = TX + 8, LDY = TY + 2 * R, PLANE = LDX * LDY;
     // margin groups of a plane: one each side of every tile row, TX / 4 per
     // row above and below the tile
-    static constexpr int NHX = 2 * TY, NHP = NHX + 2 * R * (TX / 4), NHT = NHP * BZ, NH = (NHT + NT - 1) / NT;
+    static constexpr int NHX = 2 * TY, NHP = NHX + 2 * R * (TX / 4);
     static constexpr int NQ = BZ + 2 * R;   // planes of a thread's own column
-    static_assert(NT == (TX / 4) * TY, "one 4-point group of the tile per thread");
+    static_assert(TX == 64 && NT == (TX / 4) * TY && NHP <= NT, "one group of the tile, and of a plane's margin, per thread");
 };
 
 template <int MODE>
@@ -56,19 +56,17 @@ inline constexpr bool kAdj = MODE == MODE_WAVE_ADJ || MODE == MODE_WAVE_ADJ2;
 template <int MODE, int BZ>
 inline constexpr int kBrickWaves = BZ == 2 ? 5 : kAdj<MODE> ? 3 : 4;
 
-// One workgroup's brick: tile (row by row of v.ntx) and z-chunk zch of the
-// box; rec: this workgroup records the receivers (trow >= 0).
+// One workgroup's brick: tile (tile_x, tile_y) and z-chunk zch of the box.
 template <int MODE, int R, typename T, int BZ>
-__device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3& box, int tile, int zch, bool rec,
-                                      int parity, int arow, int trow, float* __restrict__ lds) {
+__device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3& box, int tile_x, int tile_y, int zch,
+                                      int parity, int arow, float* __restrict__ lds) {
     using Z = ZBrick<R, BZ>;
     using S = Storage<T>;
-    constexpr int NT = Z::NT, TX = Z::TX, TY = Z::TY, LDX = Z::LDX, PLANE = Z::PLANE, NH = Z::NH, NQ = Z::NQ;
+    constexpr int TX = Z::TX, TY = Z::TY, LDX = Z::LDX, PLANE = Z::PLANE, NQ = Z::NQ;
     constexpr bool WAVE = MODE != MODE_HEAT;
     constexpr bool ADJ = kAdj<MODE>, ADJ2 = MODE == MODE_WAVE_ADJ2;
 
     const int tid = threadIdx.x, tx = tid % (TX / 4), ty = tid / (TX / 4);
-    const int tile_x = tile % v.ntx, tile_y = tile / v.ntx;
     // the box's x origin rounded down to a 4-element group keeps every access aligned
     const int bx = (int)box.lo[2], by = (int)box.lo[1], bz = (int)box.lo[0];
     const int X0 = (bx & ~3) + tile_x * TX, Y0 = by + tile_y * TY, zb = bz + zch * BZ;
@@ -80,51 +78,48 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
     T* O = (T*)(parity ? (void*)v.u : v.out) + v.g.origin;
     const T* B = (const T*)v.beta + v.g.origin;
 
-    // receivers sample the input level (read-only during this launch)
-    if (trow >= 0 && rec) {
-        for (int r = tid; r < v.rec.n; r += NT)
-            v.rec.trace[(int64_t)trow * v.rec.n + r] = (double)S::load(U + v.rec.off[r]);
-    }
-
-    // every load stays inside the field: planes and rows are clamped to the
-    // R-deep halo, x groups to the row; clamped values feed no stored point
+    // Every load stays inside the field: planes and rows are clamped to the
+    // R-deep halo, x groups to the row; clamped values feed no stored point.
+    // On a small grid a wave has its SIMD to itself and issues an instruction
+    // every 8 cycles, so the addresses are on the critical path: the plane's
+    // part is uniform and steps from plane to plane, a lane's is formed once
+    // for its own column and once for its margin group.
     const int xmax4 = (int)(v.g.rowlen - v.g.xlead) - 4;
     const int ymax = v.g.n[1] + R - 1, zmax = v.g.n[0] + R - 1;
     const int x0 = X0 + 4 * tx, y = Y0 + ty;
-    const T* own = U + (int64_t)min(y, ymax) * sy + min(x0, xmax4);
-    const int64_t own_off = own - U;
+    const int64_t own = (int64_t)min(y, ymax) * sy + min(x0, xmax4);
+    int64_t plane[NQ];   // offsets of planes zb - R .. zb + BZ + R - 1
+    plane[0] = (int64_t)(zb - R) * sz;
+#pragma unroll
+    for (int k = 1; k < NQ; k++) plane[k] = plane[k - 1] + (zb - R + k <= zmax ? sz : 0);
 
-    // the margins of planes zb .. zb + BZ - 1 and the thread's own column of
-    // planes zb - R .. zb + BZ + R - 1, in the storage type while in flight
+    // the thread's own column and the margins of planes zb .. zb + BZ - 1, in
+    // the storage type while in flight
     using Raw = typename RawGroup<T>::type;
-    Raw hal[NH], rq[NQ], rp[BZ], rb[BZ];
-    int hlds[NH];
+    Raw hal[BZ], rq[NQ], rp[BZ], rb[BZ];
 #pragma unroll
-    for (int k = 0; k < NQ; k++) rq[k] = load4_raw<T, false>(own + (int64_t)min(zb - R + k, zmax) * sz);
+    for (int k = 0; k < NQ; k++) rq[k] = load4_raw<T, false>(U + plane[k] + own);
+    // margin group (threads below NHP): a side of a tile row, then the rows
+    // above and below
+    const bool margin = tid < Z::NHP;
+    int hlds = 0;
+    {
+        const int t2 = tid - Z::NHX, r2 = t2 >> 4, g2 = t2 & 15;
+        const bool sides = tid < Z::NHX;
+        const int hy = sides ? Y0 + (tid >> 1) : r2 < R ? Y0 - R + r2 : Y0 + TY + (r2 - R);
+        const int hx = sides ? ((tid & 1) ? X0 + TX : X0 - 4) : X0 + 4 * g2;
+        hlds = sides ? (R + (tid >> 1)) * LDX + ((tid & 1) ? 4 + TX : 0) : (r2 < R ? r2 : TY + r2) * LDX + 4 + 4 * g2;
+        const int64_t mo = (int64_t)min(hy, ymax) * sy + min(hx, xmax4);
+        if (margin) {
 #pragma unroll
-    for (int m = 0; m < NH; m++) {
-        const int h = min(tid + m * NT, Z::NHT - 1), p = h / Z::NHP, i = h % Z::NHP;
-        int hy, hx, l;
-        if (i < Z::NHX) {
-            const int r = i >> 1, side = i & 1;
-            hy = Y0 + r;
-            hx = side ? X0 + TX : X0 - 4;
-            l = (R + r) * LDX + (side ? 4 + TX : 0);
-        } else {
-            const int r = (i - Z::NHX) / (TX / 4), g = (i - Z::NHX) % (TX / 4);
-            hy = r < R ? Y0 - R + r : Y0 + TY + (r - R);
-            hx = X0 + 4 * g;
-            l = (r < R ? r : TY + r) * LDX + 4 + 4 * g;
+            for (int p = 0; p < BZ; p++) hal[p] = load4_raw<T, false>(U + plane[R + p] + mo);
         }
-        hlds[m] = p * PLANE + l;
-        hal[m] = load4_raw<T, false>(U + (int64_t)min(zb + p, zmax) * sz + (int64_t)min(hy, ymax) * sy + min(hx, xmax4));
     }
     if constexpr (WAVE) {
 #pragma unroll
         for (int p = 0; p < BZ; p++) {
-            const int64_t zo = (int64_t)min(zb + p, zmax) * sz;
-            rp[p] = load4_raw<T, false>(P + zo + own_off);
-            rb[p] = load4_raw<T, false>(B + zo + own_off);
+            rp[p] = load4_raw<T, false>(P + plane[R + p] + own);
+            rb[p] = load4_raw<T, false>(B + plane[R + p] + own);
         }
     }
     // adjoint: the second differences and the imaging partial of the groups
@@ -154,6 +149,7 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
     // the tile's sources in this brick: entries s0 .. s1 - 1 of its z-sorted list
     int s0 = 0, s1 = 0;
     if (v.src.n > 0) {
+        const int tile = tile_y * v.ntx + tile_x;
         const int begin = ld_inv(v.src.tile_begin + tile), end = ld_inv(v.src.tile_begin + tile + 1);
         s0 = s1 = begin;
         // counted by the lanes of a wave, 64 entries at a time: a walk or a
@@ -185,9 +181,10 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
 #pragma unroll
     for (int p = 0; p < BZ; p++)
         *reinterpret_cast<float4*>(&lds[p * PLANE + (R + ty) * LDX + 4 + 4 * tx]) = q[R + p];
+    if (margin) {
 #pragma unroll
-    for (int m = 0; m < NH; m++)
-        if (tid + m * NT < Z::NHT) *reinterpret_cast<float4*>(&lds[hlds[m]]) = widen4<T>(hal[m]);
+        for (int p = 0; p < BZ; p++) *reinterpret_cast<float4*>(&lds[p * PLANE + hlds]) = widen4<T>(hal[p]);
+    }
     __syncthreads();
 
     float o[BZ][4], dv[BZ][4];
@@ -310,40 +307,84 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
     }
 }
 
-// zfast: workgroups are numbered z first, then x, y (else x, y, z)
-template <int MODE, int R, typename T, int BZ>
-__global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, int zfast, int parity,
-                                                                       int arow, int trow) {
-    __shared__ __attribute__((aligned(16))) float lds[BZ * ZBrick<R, BZ>::PLANE];
-    const int lb = xcd_remap(blockIdx.x, gridDim.x), ntxy = v.ntx * v.nty;
-    const int zch = zfast ? lb % v.nzc : lb / ntxy, tile = zfast ? lb / v.nzc : lb % ntxy;
-    brick<MODE, R, T, BZ>(v, w, box, tile, zch, lb == 0, parity, arow, trow, lds);
+// Receivers sample the input level of a launch (nothing writes it there).  They
+// have a workgroup of their own: in front of a brick their two dependent
+// loads would make that brick the last to end.
+template <typename T>
+__device__ __forceinline__ void record_input(const ZView& v, int parity, int trow) {
+    const T* U = (const T*)(parity ? v.prev : v.u) + v.g.origin;
+    double* trace = v.rec.trace + (int64_t)trow * v.rec.n;
+    for (int r = threadIdx.x; r < v.rec.n; r += 256) trace[r] = (double)Storage<T>::load(U + v.rec.off[r]);
 }
 
-// The bricks of every shot of a batch in one launch: block_map[2 b],
-// block_map[2 b + 1] = shot and block within the shot (x, y, z-chunk order) of
-// workgroup b, shot -1 for padding; the host lays it out per XCD.  A shot of
-// 100^3 has too few bricks to fill the chip and takes 6 us for 2.8 TB/s; all
+// The launch's grid: bricks numbered x, y, z or (zfast) z, x, y, one workgroup
+// more in front if receivers are recorded.
+struct BrickGrid {
+    int nb, zfast;
+    FastDiv inner, row;   // by the bricks of an xy plane (zfast: of a column); by v.ntx
+};
+
+template <int MODE, int R, typename T, int BZ>
+__global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, BrickGrid grid,
+                                                                       int parity, int arow, int trow) {
+    __shared__ __attribute__((aligned(16))) float lds[BZ * ZBrick<R, BZ>::PLANE];
+    int b = blockIdx.x;
+    // the arguments' cache lines, all asked for at once: the loads that the
+    // compiler leaves for later then find them in the scalar cache
+    asm volatile("" ::"s"(v.u), "s"(v.g.s[0]), "s"(v.src.n), "s"(v.ntx), "s"(box.lo[1]), "s"(v.rec.n), "s"(w.cd0), "s"(grid.nb));
+    if (trow >= 0) {
+        if (b == 0) {
+            record_input<T>(v, parity, trow);
+            return;
+        }
+        b--;
+    }
+    const int lb = xcd_remap(b, grid.nb);
+    const int q = (int)fdiv((uint32_t)lb, grid.inner), r = lb - q * (int)grid.inner.d;
+    const int tile = grid.zfast ? q : r, zch = grid.zfast ? r : q;
+    const int tile_y = (int)fdiv((uint32_t)tile, grid.row);
+    brick<MODE, R, T, BZ>(v, w, box, tile - tile_y * (int)grid.row.d, tile_y, zch, parity, arow, lds);
+}
+
+// The bricks of a group of shots in one launch: block_map[b] = (shot, tile x,
+// tile y, z-chunk) of workgroup b, shot -1 for padding; the host lays it out per
+// XCD.  A shot
+// of 100^3 has too few bricks to fill the chip and takes 6 us for 2.8 TB/s; all
 // shots together fill it.
 template <typename T>
 __global__ __launch_bounds__(256, (kBrickWaves<MODE_WAVE, kBatchBrick>)) void k_zbrick_batch(
-    const ZView* __restrict__ views, const int* __restrict__ block_map, Coefs w, int parity, int arow, int trow) {
+    const ZView* __restrict__ views, const int4* __restrict__ block_map, Coefs w, int parity, int arow, int trow) {
     __shared__ __attribute__((aligned(16))) float lds[kBatchBrick * ZBrick<4, kBatchBrick>::PLANE];
-    const int shot = block_map[2 * blockIdx.x], lb = block_map[2 * blockIdx.x + 1];
-    if (shot < 0) return;
-    const ZView v = views[shot];
-    const int ntxy = v.ntx * v.nty;
+    const int4 e = block_map[blockIdx.x];
+    if (e.x < 0) return;
+    // the pointers are read as constant memory, where the compiler takes them to
+    // be global; as generic ones their loads would count as LDS accesses too and
+    // every wait would be for all of them
+    const ZView* from = views + e.x;
+    ZView v = *from;
+    v.u = ld_inv(&from->u);
+    v.prev = ld_inv(&from->prev);
+    v.out = ld_inv(&from->out);
+    v.beta = ld_inv(&from->beta);
+    v.src.zyx4 = ld_inv(&from->src.zyx4);
+    v.src.amp = ld_inv(&from->src.amp);
+    v.src.scale = ld_inv(&from->src.scale);
+    v.rec.off = ld_inv(&from->rec.off);
+    v.rec.trace = ld_inv(&from->rec.trace);
     Box3 box{};
     for (int a = 0; a < 3; a++) box.n[a] = v.g.n[a];
-    brick<MODE_WAVE, 4, T, kBatchBrick>(v, w, box, lb % ntxy, lb / ntxy, lb == 0, parity, arow, trow, lds);
+    brick<MODE_WAVE, 4, T, kBatchBrick>(v, w, box, e.y, e.z, e.w, parity, arow, lds);
+    // (a workgroup in front for this, as in k_zbrick, costs 4% here: it moves
+    // the bricks of one XCD against those of the others)
+    if (trow >= 0 && (e.y | e.z | e.w) == 0) record_input<T>(v, parity, trow);
 }
 
 template <typename T>
 hipError_t brick_batch(const ZView* views, const int* block_map, int nblocks, const Coefs& w, int parity, int arow,
                        int trow, hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zbrick_batch<T>, dim3((unsigned)nblocks), dim3(256), 0, s, views, block_map, w, parity, arow,
-                       trow);
+    hipLaunchKernelGGL(k_zbrick_batch<T>, dim3((unsigned)nblocks), dim3(256), 0, s, views, (const int4*)block_map, w,
+                       parity, arow, trow);
     return hipGetLastError();
 }
 
@@ -355,9 +396,12 @@ hipError_t brick_launch(const ZView& v, const Coefs& w, const Box3& box, int par
     b.nzc = (int)((box.n[0] + BZ - 1) / BZ);
     const int64_t nb = (int64_t)b.ntx * b.nty * b.nzc;
     if (nb == 0) return hipSuccess;
-    if (nb > INT_MAX) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_zbrick<MODE, R, T, BZ>), dim3((unsigned)nb), dim3(256), 0, s, b, w, box,
-                       (int)brick_zfast(box.n, R, sizeof(T), BZ), parity, arow, trow);
+    if (nb >= INT_MAX) return hipErrorInvalidConfiguration;
+    if (v.rec.n == 0) trow = -1;
+    const bool zfast = brick_zfast(box.n, R, sizeof(T), BZ);
+    const BrickGrid grid{(int)nb, zfast, fast_div((uint32_t)(zfast ? b.nzc : b.ntx * b.nty)), fast_div((uint32_t)b.ntx)};
+    hipLaunchKernelGGL((k_zbrick<MODE, R, T, BZ>), dim3((unsigned)(nb + (trow >= 0))), dim3(256), 0, s, b, w, box, grid,
+                       parity, arow, trow);
     return hipGetLastError();
 }
 
