@@ -302,7 +302,7 @@ struct stencil_plan_s {
     // graph cache of stencil_run
     hipStream_t cap = nullptr;
     hipGraphExec_t gexec = nullptr;
-    std::vector<int64_t> gkey;
+    std::vector<int64_t> gkey;   // of the last run of two or more steps, and of gexec
     // batch
     std::vector<Layout> shots;
     std::vector<PointTables> shot_src, shot_rec;
@@ -1341,6 +1341,64 @@ static stencil_status scaled_source(DevBuf& buf, const stencil_source* src, int6
     return STENCIL_OK;
 }
 
+static stencil_status capture_run(stencil_plan p, const std::function<stencil_status(hipStream_t)>& enqueue) {
+    if (!p->cap) HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
+    HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
+    stencil_status st = enqueue(p->cap);
+    hipGraph_t graph = nullptr;
+    hipError_t e = hipStreamEndCapture(p->cap, &graph);
+    if (st != STENCIL_OK) {
+        if (graph) (void)hipGraphDestroy(graph);
+        return st;
+    }
+    if (e != hipSuccess) return fail(STENCIL_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
+    e = hipGraphInstantiate(&p->gexec, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
+    if (e != hipSuccess) {
+        p->gexec = nullptr;
+        return fail(STENCIL_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+    }
+    return STENCIL_OK;
+}
+
+// Run what `enqueue` enqueues, which `key` determines, from a captured graph
+// where the call before had the same key, else directly.  Capturing and
+// instantiating a graph takes the host longer than launching its kernels, with
+// the device idle, and is lost on a run that is not repeated, as where an odd
+// step count makes the fields change places from call to call.  Sweeps of
+// kCaptureBehind points keep the device busy longer than that: their graph is
+// captured behind the direct run, in its shadow.  Smaller ones capture on the
+// second call.  A plan's first run, captured in front / now: 100 heat steps of
+// 256^2 222 / 139 us (replayed 57), 200 wave steps of 61 x 75 x 90 1686 / 1176
+// (980), 24 of 207 x 301 x 259 in FP16 1083 / 934 (773), 32 of 8192^2 4119 /
+// 4034 (3710).
+static int64_t run_points(const stencil_plan_s* p) {
+    auto of = [](const Layout& L) { return L.extents[0] * L.extents[1] * L.extents[2]; };
+    if (!p->batch) return of(p->L);
+    int64_t sum = 0;
+    for (const Layout& L : p->shots) sum += of(L);
+    return sum;
+}
+
+constexpr int64_t kCaptureBehind = int64_t(1) << 22;
+
+static stencil_status replay(stencil_plan p, const std::vector<int64_t>& key, int64_t points,
+                             const std::function<stencil_status(hipStream_t)>& enqueue, hipStream_t s) {
+    if (key != p->gkey) {
+        if (p->gexec) {
+            HIP_TRY(hipStreamSynchronize(s));
+            HIP_TRY(hipGraphExecDestroy(p->gexec));
+            p->gexec = nullptr;
+        }
+        p->gkey = key;
+        ST_TRY(enqueue(s));
+        return points >= kCaptureBehind ? capture_run(p, enqueue) : STENCIL_OK;
+    }
+    if (!p->gexec) ST_TRY(capture_run(p, enqueue));
+    HIP_TRY(hipGraphLaunch(p->gexec, s));
+    return STENCIL_OK;
+}
+
 static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, const stencil_source* src_in,
                                  const stencil_receivers* rec, void* stream) {
     ST_TRY(run_args(p, fields, nsteps, src_in, rec));
@@ -1354,6 +1412,7 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
     void* a = fields[0];
     void* b = fields[1];
     const void* beta = p->kind == STENCIL_WAVE2 ? fields[2] : nullptr;
+    auto enqueue = [&](hipStream_t on) { return enqueue_run(p, a, b, beta, nsteps, plan_lists(p, src, rec), on); };
     if (nsteps >= 2 && graphs_enabled()) {
         std::vector<int64_t> key = {(int64_t)(uintptr_t)a,
                                     (int64_t)(uintptr_t)b,
@@ -1380,33 +1439,9 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)(uintptr_t)p->src.gbeg.buf.p,
                                     (int64_t)p->damped,
                                     (int64_t)(uintptr_t)p->damp.buf.p};
-        if (!p->gexec || key != p->gkey) {
-            if (!p->cap) HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
-            if (p->gexec) {
-                HIP_TRY(hipStreamSynchronize(s));
-                HIP_TRY(hipGraphExecDestroy(p->gexec));
-                p->gexec = nullptr;
-            }
-            HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
-            stencil_status st = enqueue_run(p, a, b, beta, nsteps, plan_lists(p, src, rec), p->cap);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(p->cap, &graph);
-            if (st != STENCIL_OK) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return st;
-            }
-            if (e != hipSuccess) return fail(STENCIL_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-            e = hipGraphInstantiate(&p->gexec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) {
-                p->gexec = nullptr;
-                return fail(STENCIL_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-            }
-            p->gkey = key;
-        }
-        HIP_TRY(hipGraphLaunch(p->gexec, s));
+        ST_TRY(replay(p, key, run_points(p), enqueue, s));
     } else {
-        ST_TRY(enqueue_run(p, a, b, beta, nsteps, plan_lists(p, src, rec), s));
+        ST_TRY(enqueue(s));
     }
     if (nsteps & 1) std::swap(fields[0], fields[1]);
     return STENCIL_OK;
@@ -2364,6 +2399,7 @@ static stencil_status batch_run_concurrent(stencil_plan p, void** fields, int64_
         return enqueue_run(p->shot_plans[sh], fields[3 * sh], fields[3 * sh + 1], fields[3 * sh + 2], nsteps, lists[sh],
                            bs);
     };
+    auto enqueue = [&](hipStream_t on) { return fork_join(p, on, bl, body); };
     if (nsteps >= 2 && graphs_enabled()) {
         std::vector<int64_t> key = {nsteps, p->variant, -1};
         for (int sh = 0; sh < ns; sh++) {
@@ -2381,33 +2417,9 @@ static stencil_status batch_run_concurrent(stencil_plan p, void** fields, int64_
             key.push_back(L.se.n);
             key.push_back(L.rl.n);
         }
-        if (!p->gexec || key != p->gkey) {
-            if (!p->cap) HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
-            if (p->gexec) {
-                HIP_TRY(hipStreamSynchronize(s));
-                HIP_TRY(hipGraphExecDestroy(p->gexec));
-                p->gexec = nullptr;
-            }
-            HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
-            stencil_status st = fork_join(p, p->cap, bl, body);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(p->cap, &graph);
-            if (st != STENCIL_OK) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return st;
-            }
-            if (e != hipSuccess) return fail(STENCIL_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-            e = hipGraphInstantiate(&p->gexec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) {
-                p->gexec = nullptr;
-                return fail(STENCIL_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-            }
-            p->gkey = key;
-        }
-        HIP_TRY(hipGraphLaunch(p->gexec, s));
+        ST_TRY(replay(p, key, run_points(p), enqueue, s));
     } else {
-        ST_TRY(fork_join(p, s, bl, body));
+        ST_TRY(enqueue(s));
     }
     if (nsteps & 1)
         for (int sh = 0; sh < ns; sh++) std::swap(fields[3 * sh], fields[3 * sh + 1]);
@@ -2457,6 +2469,7 @@ stencil_status stencil_batch_run(stencil_plan p, void** fields, int64_t nsteps, 
         if (nsteps > INT_MAX) return fail(STENCIL_E_INVALID, "the persistent batched sweep takes at most 2^31 - 1 steps");
         ST_TRY(prepare_persistent(p, var, p->hmap, p->nblocks, p->plist, p->poff));
     }
+    auto enqueue = [&](hipStream_t on) { return enqueue_batch(p, views, nsteps, var, any_rec, on); };
     if (nsteps >= 2 && graphs_enabled()) {
         std::vector<int64_t> key = {nsteps, p->variant, (int64_t)(uintptr_t)p->views.buf.p, any_rec,
                                     (int64_t)(uintptr_t)p->block_map.buf.p, (int64_t)(uintptr_t)p->ws, p->pgrid,
@@ -2475,33 +2488,9 @@ stencil_status stencil_batch_run(stencil_plan p, void** fields, int64_t nsteps, 
             key.push_back((int64_t)(uintptr_t)v.src.tile_begin);
             key.push_back((int64_t)(uintptr_t)v.rec.off);
         }
-        if (!p->gexec || key != p->gkey) {
-            if (!p->cap) HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
-            if (p->gexec) {
-                HIP_TRY(hipStreamSynchronize(s));
-                HIP_TRY(hipGraphExecDestroy(p->gexec));
-                p->gexec = nullptr;
-            }
-            HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
-            stencil_status st = enqueue_batch(p, views, nsteps, var, any_rec, p->cap);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(p->cap, &graph);
-            if (st != STENCIL_OK) {
-                if (graph) (void)hipGraphDestroy(graph);
-                return st;
-            }
-            if (e != hipSuccess) return fail(STENCIL_E_DEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-            e = hipGraphInstantiate(&p->gexec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) {
-                p->gexec = nullptr;
-                return fail(STENCIL_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
-            }
-            p->gkey = key;
-        }
-        HIP_TRY(hipGraphLaunch(p->gexec, s));
+        ST_TRY(replay(p, key, run_points(p), enqueue, s));
     } else {
-        ST_TRY(enqueue_batch(p, views, nsteps, var, any_rec, s));
+        ST_TRY(enqueue(s));
     }
     if (nsteps & 1)
         for (int sh = 0; sh < ns; sh++) std::swap(fields[3 * sh], fields[3 * sh + 1]);
