@@ -52,8 +52,8 @@ struct Grid3 {
     int64_t rowlen;  // stored elements per row (the x pitch)
 };
 
-// Point sources of one field set.  zyx4 rows are (z, y, x, index) sorted by
-// xy tile of the z-marching kernel, tile_begin is the CSR over tiles; off is
+// Point sources of one field set.  zyx4 rows are (z, y, x, index), 16-byte
+// aligned, sorted by xy tile of the kernel and then as they stand; tile_begin is the CSR over tiles; off is
 // the element offset (from the interior origin) of source `index`.
 struct SrcList {
     int n;

@@ -525,8 +525,9 @@ void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPo
     const int TX = tile_tx(cfg), TY = tile_ty(cfg);
     const int ntx = std::max(1, (L.g.n[2] + TX - 1) / TX);
     const int nty = std::max(1, (L.g.n[1] + TY - 1) / TY);
-    // sort by (xy tile, z): the kernel walks a tile's sources in z order
-    std::vector<std::tuple<int, int, int>> order;
+    // sort by (xy tile, z), as the kernels walk a tile's sources in z order,
+    // and those of one point next to each other in index order
+    std::vector<std::tuple<int, int, int64_t, int>> order;
     order.reserve((size_t)n);
     for (int64_t i = 0; i < n; i++) {
         int zyx[3];
@@ -534,7 +535,8 @@ void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPo
         const int ty0 = std::max(0, (zyx[1] - ext) / TY), ty1 = std::min(nty - 1, (zyx[1] + ext) / TY);
         const int tx0 = std::max(0, (zyx[2] - ext) / TX), tx1 = std::min(ntx - 1, (zyx[2] + ext) / TX);
         for (int ty = ty0; ty <= ty1; ty++)
-            for (int tx = tx0; tx <= tx1; tx++) order.emplace_back(ty * ntx + tx, zyx[0], (int)i);
+            for (int tx = tx0; tx <= tx1; tx++)
+                order.emplace_back(ty * ntx + tx, zyx[0], (int64_t)zyx[1] * L.g.n[2] + zyx[2], (int)i);
     }
     std::stable_sort(order.begin(), order.end());
     const int64_t m = (int64_t)order.size();
@@ -542,7 +544,7 @@ void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPo
     H.tiles.assign((size_t)ntx * nty + 1, 0);
     for (int64_t k = 0; k < m; k++) {
         int zyx[3];
-        const int i = std::get<2>(order[k]);
+        const int i = std::get<3>(order[k]);
         zyx_of(L, pos + 3 * i, zyx);
         H.zyx4[4 * k + 0] = zyx[0];
         H.zyx4[4 * k + 1] = zyx[1];
