@@ -53,8 +53,9 @@ struct Grid3 {
 };
 
 // Point sources of one field set.  zyx4 rows are (z, y, x, index), 16-byte
-// aligned, sorted by xy tile of the kernel and then as they stand; tile_begin is the CSR over tiles; off is
-// the element offset (from the interior origin) of source `index`.
+// aligned, sorted by xy tile of the kernel and then as they stand; tile_begin
+// is the CSR over tiles; off is the element offset (from the interior origin)
+// of source `index`.
 struct SrcList {
     int n;
     const int* zyx4;

@@ -143,3 +143,35 @@ def test_multistep_heat_keeps_the_halo(device, radius, shape, halo_values):
             plan.run(f, nsteps)
             r = plan.halo
             assert torch.equal(f[0].view[r:-r, r:-r], want[0].view[r:-r, r:-r]), (plan.variant_name(v), nsteps)
+
+
+@pytest.mark.parametrize("shape", [(3, 200), (40, 700)])
+@pytest.mark.parametrize("kind", [S.HEAT, S.WAVE2])
+def test_step_with_more_points_than_lanes(device, kind, shape):
+    """150 sources and receivers, most of them in one strip, some coincident: each
+    sweep adds them in the list's order and records the level that it wrote."""
+    import torch
+    rng = np.random.default_rng(9)
+    plan = S.Plan(kind, shape, 2, _weights(kind, 2))
+    plan.variant = 0
+    src, rec = (np.stack([rng.integers(0, shape[0], 150), rng.integers(0, 200, 150)], axis=1) for _ in range(2))
+    src[120:] = src[:30]
+    amp = rng.standard_normal((1, 150))
+    f = _fields(plan, 2)
+    want = plan.field()
+    want.storage.copy_(f[1].storage)
+    plan.apply(want, f)
+    level = want.view[2:-2, 2:-2].cpu().numpy()
+    for (y, x), a in zip(src, amp[0]):
+        level[y, x] = np.float32(np.float64(level[y, x]) + a)
+    trace = torch.zeros((2, 150), dtype=torch.float64, device="cuda")
+    amps = torch.tensor(np.concatenate([amp, np.zeros((1, 150))]), dtype=torch.float64, device="cuda")
+    g = [plan.field() for _ in f]
+    for a, b in zip(g, f):
+        a.storage.copy_(b.storage)
+    plan.run(f, 1, src=src, src_amp=amps[:1], rec=rec, rec_trace=trace[:1])
+    assert np.array_equal(f[0].view[2:-2, 2:-2].cpu().numpy(), level)
+    # row t of the trace is the level that step t wrote
+    plan.run(g, 2, src=src, src_amp=amps, rec=rec, rec_trace=trace)
+    rows = [a[rec[:, 0], rec[:, 1]].astype(np.float64) for a in (level, g[0].view[2:-2, 2:-2].cpu().numpy())]
+    assert np.array_equal(trace.cpu().numpy(), rows)
