@@ -1394,7 +1394,14 @@ static stencil_status replay(stencil_plan p, const std::vector<int64_t>& key, in
         }
         p->gkey = key;
         ST_TRY(enqueue(s));
-        return points >= kCaptureBehind ? capture_run(p, enqueue) : STENCIL_OK;
+        // the run is on its way: without its graph the next one goes as this one did
+        hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
+        if (points >= kCaptureBehind && hipStreamIsCapturing(s, &on) == hipSuccess && on == hipStreamCaptureStatusNone &&
+            capture_run(p, enqueue) != STENCIL_OK) {
+            (void)hipGetLastError();
+            p->gkey.clear();
+        }
+        return STENCIL_OK;
     }
     if (!p->gexec) ST_TRY(capture_run(p, enqueue));
     HIP_TRY(hipGraphLaunch(p->gexec, s));
