@@ -1439,6 +1439,7 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)(uintptr_t)p->src_ext.zyx4.buf.p,
                                     (int64_t)(uintptr_t)p->src_ext.tiles.buf.p,
                                     (int64_t)(uintptr_t)p->ws,
+                                    (int64_t)p->ws_bytes,   // decides the 2D sweep's steps per pass
                                     p->src.n,
                                     p->src.ngrp,
                                     (int64_t)p->src_ext.dense,

@@ -1,0 +1,84 @@
+"""Checks of the library's host code on the stand-in HIP calls of
+hip_stand_in.cpp, each run in a process of its own:
+
+    python _host_runtime.py <stand-in .so> <check>
+
+Fields are addresses only (no kernel runs).  The process must not load a real
+HIP runtime first, so torch is kept out of it.
+"""
+import ctypes as C
+import os
+import struct
+import sys
+import types
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FIELD0 = 1 << 40   # addresses of pretended fields
+
+
+class Host:
+    def __init__(self, stand_in):
+        self.hip = C.CDLL(stand_in, mode=C.RTLD_GLOBAL)
+        self.hip.stand_in_name.restype = C.c_char_p
+        self.hip.stand_in_arg0.restype = C.c_void_p
+        sys.modules["torch"] = types.ModuleType("torch")
+        sys.path.insert(0, ROOT)
+        import paper_2404_02218_amd as S
+        self.S, self.lib, self.next = S, S.lib(), FIELD0
+
+    def take(self, nbytes):
+        """An address range of its own, with a gap of the same size behind it."""
+        at = self.next
+        self.next += 2 * ((nbytes + 255) // 256 * 256) + 256
+        return at
+
+    def fields(self, plan, n):
+        return [self.take(plan.layout.bytes) for _ in range(n)]
+
+    def run(self, plan, fields, nsteps, src=None, rec=None, name="stencil_run", stream=None):
+        ptrs = (C.c_void_p * 3)(*fields + [0] * (3 - len(fields)))
+        st = getattr(self.lib, name)(plan.handle, ptrs, nsteps, C.byref(src) if src else None,
+                                     C.byref(rec) if rec else None, stream)
+        return st, [ptrs[i] for i in range(len(fields))]
+
+    def launches(self):
+        """(kernel name, grid, first bytes of the first argument) since the last call."""
+        out = [(self.hip.stand_in_name(i).decode(), self.hip.stand_in_grid(i),
+                C.string_at(self.hip.stand_in_arg0(i), 128)) for i in range(self.hip.stand_in_launches())]
+        self.hip.stand_in_clear()
+        return out
+
+    def counts(self):
+        c = (C.c_int * 9)()
+        self.hip.stand_in_counts(c)
+        return dict(zip(("captures", "instantiated", "replays", "syncs", "execs", "graphs", "events", "streams",
+                         "blocks"), c))
+
+
+def _outputs(launch):
+    """The fields a launch of the 2D sweep writes: u, prev, beta, out, out1 lead its descriptor."""
+    return [p for p in struct.unpack("8Q", launch[2][:64])[3:5] if p]
+
+
+def shrunk_workspace(h):
+    """A workspace attached again with fewer bytes, at the same address, is not written past them."""
+    S = h.S
+    plan = S.Plan(S.WAVE2, (3000, 3013), 4, S.second_derivative_weights(8))
+    f, need = h.fields(plan, 3), plan.run_workspace_bytes()
+    assert need > 0
+    ws = h.take(need)
+    for nbytes in (need, 4096, need, need // 2, 0, need):
+        S.call("stencil_set_workspace", plan.handle, C.c_void_p(ws if nbytes else None), nbytes, None)
+        h.launches()
+        for _ in range(3):
+            assert h.run(plan, f, 16)[0] == 0
+            swept = [x for x in h.launches() if "2d" in x[0]]
+            written = {p for x in swept for p in _outputs(x)} - set(f[:2])
+            assert bool(written) == (nbytes == need) == any("k_march2d" in x[0] for x in swept)
+            for p in written:
+                assert ws <= p and p + plan.layout.bytes <= ws + nbytes
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]](Host(sys.argv[1]))
+    print("ok")

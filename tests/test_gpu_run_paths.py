@@ -1,0 +1,64 @@
+"""Runs that change their route between calls: an attached workspace that
+shrinks, against runs of single steps."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import paper_2404_02218_amd as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(kind, radius):
+    return S.heat_weights(2 * radius, 0.05) if kind == S.HEAT else S.second_derivative_weights(2 * radius)
+
+
+def _fields(plan, seed):
+    """Random levels (and beta), zero halos."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    h, f = plan.halo, [plan.field() for _ in range(3 if plan.kind == S.WAVE2 else 2)]
+    inner = (slice(h, -h),) * plan.ndim
+    for x in f[:2]:
+        x.view[inner] = torch.randn(plan.shape, generator=g, device="cuda").to(x.view.dtype)
+    if len(f) > 2:
+        f[2].view.copy_(torch.rand(f[2].view.shape, generator=g, device="cuda") * 0.05)
+    return f
+
+
+def _bits(f):
+    import torch
+    return f.view.contiguous().view(torch.int32 if f.dtype == S.F32 else torch.int16)
+
+
+def _same(a, b):
+    import torch
+    return all(torch.equal(_bits(x), _bits(y)) for x, y in zip(a, b))
+
+
+def _run(plan, f, nsteps):
+    """stencil_run itself, with the workspace that is attached."""
+    ptrs = (C.c_void_p * 3)(*[x.ptr for x in f] + [0] * (3 - len(f)))
+    S.call("stencil_run", plan.handle, ptrs, nsteps, None, None, None)
+    if ptrs[0] != f[0].ptr:
+        f[0], f[1] = f[1], f[0]
+
+
+def test_a_shrunk_workspace_is_not_written_past_its_end(device):
+    import torch
+    plan = S.Plan(S.WAVE2, (1000, 1003), 1, _weights(S.WAVE2, 1))
+    need = plan.run_workspace_bytes()
+    assert need > 0
+    buf = torch.full((need,), 0x5a, dtype=torch.uint8, device=device)
+    f, want = _fields(plan, 3), _fields(plan, 3)
+    for nbytes in (need, need // 2, need, 4096):
+        S.call("stencil_set_workspace", plan.handle, C.c_void_p(buf.data_ptr()), nbytes, None)
+        buf[nbytes:] = 0x5a
+        for _ in range(3):
+            _run(plan, f, 16)
+        S.call("stencil_set_workspace", plan.handle, None, 0, None)
+        for _ in range(48):
+            _run(plan, want, 1)
+        assert torch.all(buf[nbytes:] == 0x5a)
+        assert _same(f, want)

@@ -1,0 +1,29 @@
+"""The library's host code without a GPU: what it launches, captures, replays
+and keeps, on the stand-in HIP calls of hip_stand_in.cpp (checks in
+_host_runtime.py, each in a process of its own)."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ is not available")
+    lib = str(tmp_path_factory.mktemp("hip") / "libhip_stand_in.so")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-fPIC", "-shared", "-Wall", "-o", lib,
+                    os.path.join(HERE, "hip_stand_in.cpp")], check=True)
+    return lib
+
+
+@pytest.mark.parametrize("check", ["shrunk_workspace"])
+def test_host_runtime(stand_in, check):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "_host_runtime.py"), stand_in, check], capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.endswith("ok\n"), (r.stdout + r.stderr)[-4000:]
