@@ -79,6 +79,44 @@ def shrunk_workspace(h):
                 assert ws <= p and p + plan.layout.bytes <= ws + nbytes
 
 
+def _batch(h, sides, variant):
+    S = h.S
+    batch = S.BatchPlan(sides, 4, S.second_derivative_weights(8))
+    batch.variant = next(v for v in range(batch.variant_count()) if batch.variant_name(v) == variant)
+    return batch, [h.take(layout.bytes) for layout in batch.layouts for _ in range(3)]
+
+
+def _run_batch(h, batch, fields, nsteps, stream=None):
+    ptrs = (C.c_void_p * len(fields))(*fields)
+    st = h.lib.stencil_batch_run(batch._h, ptrs, nsteps, None, None, stream)
+    return st, list(ptrs)
+
+
+def concurrent_batch(h):
+    """Concurrent shots whose step count, buffers and variant change: one graph of four branches in the life
+    of a plan, every launch in the run's own number and order of steps, and no handle left when it ends."""
+    for sides in ([(20, 24, 28), (36, 40, 44), (17, 18, 19)], [(170, 170, 170), (60, 60, 60)]):   # past 2^22 points
+        before = h.counts()
+        batch, f = _batch(h, sides, "shots_concurrent_4")
+        fused = next(v for v in range(batch.variant_count()) if batch.variant_name(v).startswith("zmarch_64x32"))
+        concurrent = batch.variant
+        for n in [7, 7, 38, 39, 40, 40, 40, 38, 39, 40, 2, 2, 2, 3, 4, 5, 6, 40, 40, 40]:
+            h.launches()
+            st, f = _run_batch(h, batch, f, n)
+            assert st == 0
+            assert sum("k_zbrick" in x[0] for x in h.launches()) == n * len(sides)
+        for v in (fused, concurrent, fused, concurrent):
+            batch.variant = v
+            for _ in range(3):
+                assert _run_batch(h, batch, f, 4)[0] == 0
+        branched = h.counts()["captures"] - before["captures"]
+        assert branched == 1 + 2   # and one of each run of the fused variant
+        del batch
+        after = h.counts()
+        assert {k: after[k] for k in ("execs", "graphs", "events", "streams", "blocks")} == \
+               {k: before[k] for k in ("execs", "graphs", "events", "streams", "blocks")}
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")
