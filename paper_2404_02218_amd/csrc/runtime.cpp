@@ -303,6 +303,7 @@ struct stencil_plan_s {
     hipStream_t cap = nullptr;
     hipGraphExec_t gexec = nullptr;
     std::vector<int64_t> gkey;   // of the last run of two or more steps, and of gexec
+    bool glaunched = false;      // gexec has been launched
     // batch
     std::vector<Layout> shots;
     std::vector<PointTables> shot_src, shot_rec;
@@ -1364,17 +1365,7 @@ static stencil_status capture_run(stencil_plan p, const std::function<stencil_st
     return STENCIL_OK;
 }
 
-// Run what `enqueue` enqueues, which `key` determines, from a captured graph
-// where the call before had the same key, else directly.  Capturing and
-// instantiating a graph takes the host longer than launching its kernels, with
-// the device idle, and is lost on a run that is not repeated, as where an odd
-// step count makes the fields change places from call to call.  Sweeps of
-// kCaptureBehind points keep the device busy longer than that: their graph is
-// captured behind the direct run, in its shadow.  Smaller ones capture on the
-// second call.  A plan's first run, captured in front / now: 100 heat steps of
-// 256^2 222 / 139 us (replayed 57), 200 wave steps of 61 x 75 x 90 1686 / 1176
-// (980), 24 of 207 x 301 x 259 in FP16 1083 / 934 (773), 32 of 8192^2 4119 /
-// 4034 (3710).
+// interior and halo points of a plan's fields
 static int64_t run_points(const stencil_plan_s* p) {
     auto of = [](const Layout& L) { return L.extents[0] * L.extents[1] * L.extents[2]; };
     if (!p->batch) return of(p->L);
@@ -1385,38 +1376,58 @@ static int64_t run_points(const stencil_plan_s* p) {
 
 constexpr int64_t kCaptureBehind = int64_t(1) << 22;
 
-// once: the plan captures such a run a single time, at a second call in a row,
-// and enqueues runs with another key directly from then on.  The concurrent
-// batch asks for it: a process that captured its four branches some twenty
-// times, with another step count each, was ended by the C library's check of
-// its heap.  The lifetimes of the streams, events and graphs are right by
-// reading and by the stand-in test, so the cause is not known, and repeated
-// captures of the branches stay out.
-static stencil_status replay(stencil_plan p, const std::vector<int64_t>& key, int64_t points,
+// Run what `enqueue` enqueues, which `key` determines: directly the first time,
+// from a captured graph where calls with the same key follow each other.
+// Capturing and instantiating a graph takes the host longer than launching its
+// kernels, with the device idle, and is lost on a run that is not repeated, as
+// where an odd step count makes the fields change places from call to call.  So
+// the second call in a row captures: behind its own launches for sweeps of
+// kCaptureBehind points, which keep the device busy meanwhile, and before them
+// for smaller ones.  A plan's first run, captured in front / direct: 100 heat
+// steps of 256^2 222 / 139 us (replayed 57), 200 wave steps of 61 x 75 x 90
+// 1686 / 1176 (980), 24 of 207 x 301 x 259 in FP16 1083 / 934 (773), 32 of
+// 8192^2 4119 / 4034 (3710).
+//
+// On a stream that the caller is capturing, the launches go into that capture
+// and the plan's own graph stays as it is.
+//
+// once: the plan captures such a run a single time and enqueues directly where
+// the key changes after that.  The concurrent batch asks for it: a process that
+// captured its four branches some twenty times, with another step count each,
+// was ended by the C library's check of its heap.  The lifetimes of the
+// streams, events and graphs are right by reading and by the stand-in test, so
+// the cause is not known, and repeated captures of the branches stay out.
+static stencil_status replay(stencil_plan p, const std::vector<int64_t>& key,
                              const std::function<stencil_status(hipStream_t)>& enqueue, hipStream_t s,
                              bool once = false) {
+    hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &on) != hipSuccess) (void)hipGetLastError();
+    if (on != hipStreamCaptureStatusNone) return enqueue(s);
     if (key != p->gkey) {
         if (p->gexec) {
-            HIP_TRY(hipStreamSynchronize(s));
+            if (p->glaunched) HIP_TRY(hipStreamSynchronize(s));
             HIP_TRY(hipGraphExecDestroy(p->gexec));
             p->gexec = nullptr;
         }
         p->gkey = key;
-        ST_TRY(enqueue(s));
-        // the run is on its way: without its graph the next one goes as this one did
-        hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
-        if (!once && points >= kCaptureBehind && hipStreamIsCapturing(s, &on) == hipSuccess && on == hipStreamCaptureStatusNone &&
-            capture_run(p, enqueue) != STENCIL_OK) {
-            (void)hipGetLastError();
-            p->gkey.clear();
-        }
-        return STENCIL_OK;
+        return enqueue(s);
     }
     if (!p->gexec) {
         if (once && p->branch_captured) return enqueue(s);
         p->branch_captured |= once;
+        p->glaunched = false;
+        if (run_points(p) >= kCaptureBehind && !once) {
+            ST_TRY(enqueue(s));
+            // the run is on its way: without its graph the next one goes as this one did
+            if (capture_run(p, enqueue) != STENCIL_OK) {
+                (void)hipGetLastError();
+                p->gkey.clear();
+            }
+            return STENCIL_OK;
+        }
         ST_TRY(capture_run(p, enqueue));
     }
+    p->glaunched = true;
     HIP_TRY(hipGraphLaunch(p->gexec, s));
     return STENCIL_OK;
 }
@@ -1462,7 +1473,7 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)(uintptr_t)p->src.gbeg.buf.p,
                                     (int64_t)p->damped,
                                     (int64_t)(uintptr_t)p->damp.buf.p};
-        ST_TRY(replay(p, key, run_points(p), enqueue, s));
+        ST_TRY(replay(p, key, enqueue, s));
     } else {
         ST_TRY(enqueue(s));
     }
@@ -2440,7 +2451,7 @@ static stencil_status batch_run_concurrent(stencil_plan p, void** fields, int64_
             key.push_back(L.se.n);
             key.push_back(L.rl.n);
         }
-        ST_TRY(replay(p, key, run_points(p), enqueue, s, true));
+        ST_TRY(replay(p, key, enqueue, s, true));
     } else {
         ST_TRY(enqueue(s));
     }
@@ -2511,7 +2522,7 @@ stencil_status stencil_batch_run(stencil_plan p, void** fields, int64_t nsteps, 
             key.push_back((int64_t)(uintptr_t)v.src.tile_begin);
             key.push_back((int64_t)(uintptr_t)v.rec.off);
         }
-        ST_TRY(replay(p, key, run_points(p), enqueue, s));
+        ST_TRY(replay(p, key, enqueue, s));
     } else {
         ST_TRY(enqueue(s));
     }

@@ -117,6 +117,77 @@ def concurrent_batch(h):
                {k: before[k] for k in ("execs", "graphs", "events", "streams", "blocks")}
 
 
+def _delta(h, before):
+    return {k: n - before[k] for k, n in h.counts().items()}
+
+
+def runs_that_are_not_repeated(h):
+    """Runs whose arguments change from call to call (an odd step count makes the fields change places) cost no
+    graph and wait for nothing; the second run in a row with the same arguments captures, the third replays."""
+    S = h.S
+    for shape in ((170, 170, 170), (40, 44, 48), (2100, 2050)):   # the first and last past 2^22 points
+        plan = S.Plan(S.WAVE2, shape, 4, S.second_derivative_weights(8))
+        plan.variant = 0
+        f = h.fields(plan, 3)
+        before = h.counts()
+        for n in (5, 5, 7, 7, 7, 3, 4, 6, 4, 6):
+            h.launches()
+            st, f = h.run(plan, f, n)
+            assert st == 0 and len(h.launches()) == n
+        d = _delta(h, before)
+        assert d["captures"] == 0 and d["syncs"] == 0, d
+        want = None
+        for k in range(5):   # direct, captured, replayed
+            assert h.run(plan, f, 8)[0] == 0
+            got = h.launches()
+            assert len(got) == 8 and (want is None or got == want), shape
+            want = got
+        d = _delta(h, before)
+        assert (d["captures"], d["execs"]) == (1, 1) and d["replays"] >= 3
+        # a graph that was never launched is not waited for
+        assert h.run(plan, f, 6)[0] == 0 and h.run(plan, f, 6)[0] == 0
+        waited = h.counts()["syncs"]
+        assert h.run(plan, f, 8)[0] == 0
+        assert h.counts()["syncs"] - waited == (0 if _delta(h, before)["replays"] == d["replays"] else 1)
+        del plan
+
+
+def runs_in_a_caller_capture(h):
+    """Runs on a stream that the caller is capturing are enqueued into that capture, whatever the plan has kept:
+    nothing is waited for, no graph of the plan's is destroyed or launched there."""
+    S = h.S
+    stream = C.c_void_p()
+    h.hip.hipStreamCreateWithFlags(C.byref(stream), 0)
+    for shape in ((170, 170, 170), (40, 44, 48)):
+        for kept in (1, 2, 3):   # runs before the capture (the first one uploads the plan's tables)
+            plan = S.Plan(S.WAVE2, shape, 4, S.second_derivative_weights(8))
+            plan.variant = 0
+            f = h.fields(plan, 3)
+            for _ in range(kept):
+                assert h.run(plan, f, 4, stream=stream)[0] == 0
+            h.launches()
+            before = h.counts()
+            assert h.hip.hipStreamBeginCapture(stream, 0) == 0
+            for n in (4, 6, 4, 6, 6):
+                assert h.run(plan, f, n, stream=stream)[0] == 0, h.lib.stencil_last_error()
+            graph = C.c_void_p()
+            assert h.hip.hipStreamEndCapture(stream, C.byref(graph)) == 0 and graph.value
+            assert not h.launches()   # all of it went into the capture
+            d = _delta(h, before)
+            assert (d["captures"], d["execs"], d["replays"], d["syncs"]) == (1, 0, 0, 0), d
+            x = C.c_void_p()
+            assert h.hip.hipGraphInstantiate(C.byref(x), graph, None, None, C.c_size_t(0)) == 0
+            assert h.hip.hipGraphLaunch(x, stream) == 0
+            got = h.launches()
+            assert len(got) == 26
+            for n in (4, 6, 4, 6, 6):   # the same launches as outside
+                assert h.run(plan, f, n)[0] == 0
+            assert [g[2] for g in h.launches()] == [g[2] for g in got]
+            h.hip.hipGraphExecDestroy(x)
+            h.hip.hipGraphDestroy(graph)
+            del plan
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")

@@ -1,5 +1,5 @@
-"""Runs that change their route between calls: an attached workspace that
-shrinks, against runs of single steps."""
+"""Runs that change their route between calls (an attached workspace that
+shrinks, a capture of the caller's), against plain runs."""
 import ctypes as C
 
 import numpy as np
@@ -62,3 +62,46 @@ def test_a_shrunk_workspace_is_not_written_past_its_end(device):
             _run(plan, want, 1)
         assert torch.all(buf[nbytes:] == 0x5a)
         assert _same(f, want)
+
+
+@pytest.mark.parametrize("kind,shape", [(S.WAVE2, (40, 44, 72)), (S.WAVE2, (162, 162, 162)), (S.HEAT, (70, 90)),
+                                        (S.WAVE2, (2100, 2050))])
+@pytest.mark.parametrize("kept", [1, 3])
+def test_runs_in_a_caller_capture(device, kind, shape, kept):
+    """Runs captured by the caller, before and after the plan has a graph of its own, replayed three times with
+    eager work between."""
+    import torch
+    n, rng = 6, np.random.default_rng(5)
+    src = np.stack([rng.integers(0, k, 3) for k in shape], axis=1)
+    rec = np.stack([rng.integers(0, k, 9) for k in shape], axis=1)
+    amp = torch.from_numpy(rng.standard_normal((n, 3))).cuda()
+    plan = S.Plan(kind, shape, 2, _weights(kind, 2))
+    plan.variant = 0
+    points = dict(src=src, src_amp=amp, rec=rec)
+
+    def passes(f, trace, captured):
+        inner = (slice(2, -2),) * len(shape)
+        out, graph = [], None
+        for _ in range(kept):
+            plan.run(f, n, rec_trace=trace, **points)
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                plan.run(f, n, rec_trace=trace, **points)
+                plan.run(f, n, rec_trace=trace, **points)
+        for k in range(3):
+            f[0].view[inner] *= 0.5 + 0.1 * k
+            if captured:
+                graph.replay()
+            else:
+                plan.run(f, n, rec_trace=trace, **points)
+                plan.run(f, n, rec_trace=trace, **points)
+            torch.cuda.synchronize()
+            out.append([x.view.clone() for x in f] + [trace.clone()])
+        return out
+
+    trace = torch.zeros((n, 9), dtype=torch.float64, device=device)
+    got = passes(_fields(plan, 7), trace, True)
+    want = passes(_fields(plan, 7), trace, False)
+    for a, b in zip(got, want):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
