@@ -165,7 +165,9 @@ stencil_status stencil_apply(stencil_plan plan, void* out, const void* const* in
  * level (and, for the wave, fields[1] the one before).  With periodic
  * boundaries the halo of the current level is refreshed before each sweep by
  * a self-exchange (the dmp.swap of a one-rank periodic grid, Section 4.2).
- * src/rec may be NULL.  The launches of a run of two or more steps are
+ * src/rec may be NULL.  The multi-step heat variants serve runs without them;
+ * a heat run with sources or receivers takes plain sweeps (the same bits).
+ * The launches of a run of two or more steps are
  * captured into one HIP graph per (pointers, nsteps, variant, tables) at the
  * second call in a row, and replayed from then on (on a stream that the caller
  * is capturing they go into that capture); with the environment variable STENCIL_NO_GRAPH set to a value

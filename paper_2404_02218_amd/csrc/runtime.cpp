@@ -164,6 +164,7 @@ struct Variant {
     bool tb = false;   // depth-2 temporal blocking (tile 64 x 32 = tile shape 0)
     bool persistent = false;   // batch: every step in one launch with grid barriers
     bool march2d = false;      // the 2D sweep by strips
+    bool heat2d = false;       // the multi-step 2D heat sweep, configuration cfg
     int cfg = 0;
     int zc = 0;
 };
@@ -431,6 +432,12 @@ Variant plan_variant(const stencil_plan_s* p, int v) {
         r.march2d = true;
         return r;
     }
+    if (heat2d_supported(p)) {
+        Variant r;
+        r.heat2d = true;
+        r.cfg = v - 1;
+        return r;
+    }
     if (batch_bricks(p, v)) {
         Variant r;
         r.zmarch = true;
@@ -445,6 +452,23 @@ Variant plan_variant(const stencil_plan_s* p, int v) {
     r.cfg = kPersistentCfg;
     r.zc = kZChunks[v - (variant_count_of(p) - 1 - kNumPersistent)];
     return r;
+}
+
+// The variant of a run with or without points (sources or receivers).  The
+// multi-step heat sweeps take none: with points a 2D run goes by strips and a
+// 3D one in plain sweeps on the same tiles.
+Variant run_variant(const stencil_plan_s* p, bool points) {
+    Variant r = plan_variant(p, p->variant);
+    if (p->kind != STENCIL_HEAT || !points) return r;
+    if (r.heat2d) return plan_variant(p, 0);
+    if (r.tb) {
+        r.tb = false;
+        r.zmarch = true;
+    }
+    return r;
+}
+bool has_points(const stencil_source* src, const stencil_receivers* rec) {
+    return (src && src->n > 0) || (rec && rec->n > 0);
 }
 
 // plans of the sweep entry points (not stencil programs)
@@ -885,8 +909,7 @@ stencil_status enqueue_run_tb(stencil_plan p, const Variant& var, void* a, void*
 // 2D heat with the multi-step kernel: as few passes between the two buffers as
 // the kernel's depth allows, odd in number when nsteps is (the newest level
 // then lands where nsteps plain sweeps would leave it), of nearly equal steps.
-static stencil_status enqueue_run_heat2d(stencil_plan p, void* a, void* b, int64_t nsteps, hipStream_t s) {
-    const int cfg = p->variant - 1;
+static stencil_status enqueue_run_heat2d(stencil_plan p, int cfg, void* a, void* b, int64_t nsteps, hipStream_t s) {
     const int64_t T = kHeat2dCfgs[cfg].t;
     int64_t passes = (nsteps + T - 1) / T;
     if ((passes ^ nsteps) & 1) passes++;
@@ -959,12 +982,12 @@ static stencil_status enqueue_run_march2d(stencil_plan p, void* a, void* b, cons
     return STENCIL_OK;
 }
 
-// Enqueue nsteps sweeps of a single plan (no capture logic here).
-stencil_status enqueue_run(stencil_plan p, void* a, void* b, const void* beta, int64_t nsteps,
+// Enqueue nsteps sweeps of a single plan (no capture logic here).  var: the
+// run's variant, for which its lists were made.
+stencil_status enqueue_run(stencil_plan p, Variant var, void* a, void* b, const void* beta, int64_t nsteps,
                            const RunLists& RL, hipStream_t s) {
     const Layout& L = p->L;
-    if (p->ndim == 2 && p->variant > 0 && heat2d_supported(p)) return enqueue_run_heat2d(p, a, b, nsteps, s);
-    Variant var = plan_variant(p, p->variant);
+    if (var.heat2d) return enqueue_run_heat2d(p, var.cfg, a, b, nsteps, s);
     const bool wave = p->kind == STENCIL_WAVE2;
     if (var.march2d) return enqueue_run_march2d(p, a, b, beta, nsteps, RL, s);
     if (var.tb && wave) return enqueue_run_tb(p, var, a, b, beta, nsteps, RL, s);
@@ -1013,6 +1036,8 @@ stencil_status enqueue_run(stencil_plan p, void* a, void* b, const void* beta, i
             v.rec = rl;
             const int trow = (rl.n > 0 && t >= 1) ? (int)(t - 1) : -1;
             HIP_TRY(launch_zmarch(mode, p->radius, p->dtype, var.cfg, v, p->w, parity, (int)t, trow, s));
+            // the z-marching heat kernels take no sources
+            if (!wave && var.cfg != kBrickCfg && sl.n) HIP_TRY(launch_inject(p->dtype, nxt, L.g, sl, (int)t, s));
         } else {
             ZView v{};
             v.u = cur;
@@ -1269,8 +1294,8 @@ static stencil_status run_args(stencil_plan p, void** fields, int64_t nsteps, co
     return STENCIL_OK;
 }
 
-static stencil_status prepare_points(stencil_plan p, const stencil_source* src, const stencil_receivers* rec) {
-    const Variant var = plan_variant(p, p->variant);
+static stencil_status prepare_points(stencil_plan p, const Variant& var, const stencil_source* src,
+                                     const stencil_receivers* rec) {
     if (var.march2d) {
         HostPoints H;
         const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
@@ -1437,7 +1462,8 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
     ST_TRY(run_args(p, fields, nsteps, src_in, rec));
     ST_TRY(check_source_scale(src_in));
     ST_TRY(check_workspace(p));
-    ST_TRY(prepare_points(p, src_in, rec));
+    const Variant var = run_variant(p, has_points(src_in, rec));
+    ST_TRY(prepare_points(p, var, src_in, rec));
     hipStream_t s = (hipStream_t)stream;
     stencil_source scaled{};
     const stencil_source* src = src_in;
@@ -1445,13 +1471,14 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
     void* a = fields[0];
     void* b = fields[1];
     const void* beta = p->kind == STENCIL_WAVE2 ? fields[2] : nullptr;
-    auto enqueue = [&](hipStream_t on) { return enqueue_run(p, a, b, beta, nsteps, plan_lists(p, src, rec), on); };
+    auto enqueue = [&](hipStream_t on) { return enqueue_run(p, var, a, b, beta, nsteps, plan_lists(p, src, rec), on); };
     if (nsteps >= 2 && graphs_enabled()) {
         std::vector<int64_t> key = {(int64_t)(uintptr_t)a,
                                     (int64_t)(uintptr_t)b,
                                     (int64_t)(uintptr_t)beta,
                                     nsteps,
                                     p->variant,
+                                    has_points(src, rec),
                                     (int64_t)(uintptr_t)(src ? src->amp : nullptr),
                                     (int64_t)(uintptr_t)(rec ? rec->trace : nullptr),
                                     (int64_t)(uintptr_t)p->src.off.buf.p,
@@ -1488,7 +1515,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     ST_TRY(check_source_scale(src));
     ST_TRY(check_workspace(p));
     const Layout& L = p->L;
-    const Variant var = plan_variant(p, p->variant);
+    const Variant var = run_variant(p, has_points(src, rec));
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
     HostPoints hs, he, hr;
@@ -1540,7 +1567,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     RL.rl.trace = nr ? rec->trace : nullptr;
     RL.rl.zyx4 = (const int*)pr.zyx4;
     RL.rl.tile_begin = (const int*)pr.tiles;
-    ST_TRY(enqueue_run(p, fields[0], fields[1], p->kind == STENCIL_WAVE2 ? fields[2] : nullptr, nsteps, RL, s));
+    ST_TRY(enqueue_run(p, var, fields[0], fields[1], p->kind == STENCIL_WAVE2 ? fields[2] : nullptr, nsteps, RL, s));
     if (nsteps & 1) std::swap(fields[0], fields[1]);
     return STENCIL_OK;
 }
@@ -2423,15 +2450,16 @@ static stencil_status batch_run_concurrent(stencil_plan p, void** fields, int64_
         wsp += need;
         const stencil_source* ss = src ? &src[sh] : nullptr;
         const stencil_receivers* rr = rec ? &rec[sh] : nullptr;
-        ST_TRY(prepare_points(q, ss, rr));
+        ST_TRY(prepare_points(q, plan_variant(q, q->variant), ss, rr));
         const stencil_source* use = ss;
         ST_TRY(scaled_source(q->amp_scaled, ss, nsteps, scaled[sh], use, s));
         lists[sh] = plan_lists(q, use, rr);
     }
     const std::vector<std::vector<int>> bl = branch_lists(p);
     auto body = [&](hipStream_t bs, int sh) -> stencil_status {
-        return enqueue_run(p->shot_plans[sh], fields[3 * sh], fields[3 * sh + 1], fields[3 * sh + 2], nsteps, lists[sh],
-                           bs);
+        stencil_plan q = p->shot_plans[sh];
+        return enqueue_run(q, plan_variant(q, q->variant), fields[3 * sh], fields[3 * sh + 1], fields[3 * sh + 2], nsteps,
+                           lists[sh], bs);
     };
     auto enqueue = [&](hipStream_t on) { return fork_join(p, on, bl, body); };
     if (nsteps >= 2 && graphs_enabled()) {

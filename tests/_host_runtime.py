@@ -188,6 +188,42 @@ def runs_in_a_caller_capture(h):
             del plan
 
 
+def _points(h, shape, n, step=1):
+    """A list of n points of the grid, its positions kept alive with it."""
+    pos = (C.c_int64 * (3 * n))()
+    for k in range(n):
+        at = k * step
+        for d in range(len(shape) - 1, -1, -1):
+            pos[3 * k + d] = at % shape[d]
+            at //= shape[d]
+    return pos
+
+
+def heat_points(h):
+    """A heat run with sources or receivers takes a sweep that serves them, whatever the variant; one without
+    takes the multi-step sweep that the variant names.  So does the run without allocations."""
+    S = h.S
+    for shape, radius, multi in (((70, 90), 1, "k_heat2d_tb"), ((1300, 1301), 2, "k_heat2d_tb"), ((40, 44, 72), 2, "k_tb2")):
+        plan = S.Plan(S.HEAT, shape, radius, S.heat_weights(2 * radius, 0.05))
+        pos = _points(h, shape, 3, 1237)
+        src = S.Source(3, C.cast(pos, C.c_void_p), C.c_void_p(4096), None)
+        rec = S.Receivers(3, C.cast(pos, C.c_void_p), C.c_void_p(8192))
+        f, seen = h.fields(plan, 2), 0
+        for v in range(plan.variant_count()):
+            plan.variant = v
+            for name in ("stencil_run", "stencil_run_noalloc"):
+                deep = []
+                for points in ({}, {"src": src}, {"rec": rec}, {"src": src, "rec": rec}):
+                    h.launches()
+                    assert h.run(plan, f, 8, name=name, **points)[0] == 0
+                    swept = [x[0] for x in h.launches() if "k_fill" not in x[0]]
+                    assert swept
+                    deep.append(any(multi in x for x in swept))
+                assert deep[1:] == [False] * 3, (plan.variant_name(v), name, deep)
+                seen += deep[0]
+        assert seen > 0
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")

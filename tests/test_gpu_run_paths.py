@@ -105,3 +105,38 @@ def test_runs_in_a_caller_capture(device, kind, shape, kept):
     want = passes(_fields(plan, 7), trace, False)
     for a, b in zip(got, want):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("shape,radius", [((70, 90), 1), ((130, 75), 2), ((1400, 1203), 1), ((20, 40, 70), 2)])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_heat_points_are_served_by_every_variant(device, shape, radius, noalloc):
+    """Sources and receivers of a heat run at every variant and the default one, against single steps."""
+    import torch
+    n, rng = 9, np.random.default_rng(4)
+    src = np.stack([rng.integers(0, k, 5) for k in shape], axis=1)
+    src[4] = src[2]
+    rec = np.stack([rng.integers(0, k, 80) for k in shape], axis=1)
+    rec[:5] = src
+    amp = torch.from_numpy(rng.standard_normal((n, 5))).cuda()
+    plan = S.Plan(S.HEAT, shape, radius, _weights(S.HEAT, radius))
+    default = plan.variant
+
+    def run(f, t0, n):
+        trace = torch.zeros((n, 80), dtype=torch.float64, device=device)
+        sp, rp = S._Points(src, amp[t0:t0 + n].contiguous()), S._Points(rec, trace)
+        ptrs = (C.c_void_p * 3)(*[x.ptr for x in f] + [0])
+        S.call("stencil_run_noalloc" if noalloc else "stencil_run", plan.handle, ptrs, n, C.byref(sp.source()),
+               C.byref(rp.receivers()), None)
+        torch.cuda.synchronize()
+        if ptrs[0] != f[0].ptr:
+            f[0], f[1] = f[1], f[0]
+        return trace
+
+    plan.variant = 0
+    want = _fields(plan, 2)
+    rows = torch.cat([run(want, t, 1) for t in range(n)])
+    for v in [default] + list(range(plan.variant_count())):
+        plan.variant = v
+        f = _fields(plan, 2)
+        assert torch.equal(run(f, 0, n), rows), plan.variant_name(v)
+        assert _same(f[:1], want[:1]), plan.variant_name(v)
