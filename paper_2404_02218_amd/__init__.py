@@ -133,19 +133,29 @@ def _real_positions(pos, ndim):
 
 class _Workspace:
     """Caller memory for a plan's run workspace (stencil_run_workspace /
-    stencil_set_workspace), grown when the plan's variant needs more."""
+    stencil_set_workspace), grown when the plan's variant needs more.  A plan
+    that also runs without one (`optional`) does so where the memory is short."""
 
     def __init__(self):
         self.buf = None
+        self.declined = None   # the size that the device had no room for
 
-    def ensure(self, handle, stream=None):
+    def ensure(self, handle, stream=None, optional=False):
         b = C.c_size_t()
         call("stencil_run_workspace", handle, C.byref(b))
         need = b.value
         if need == 0 or (self.buf is not None and self.buf.numel() >= need):
             return
+        if optional and self.declined == need:
+            return
         torch = _torch()
-        self.buf = torch.empty(need, dtype=torch.uint8, device=torch.cuda.current_device())
+        try:
+            self.buf = torch.empty(need, dtype=torch.uint8, device=torch.cuda.current_device())
+        except torch.cuda.OutOfMemoryError:
+            if not optional:
+                raise
+            self.declined = need
+            return
         call("stencil_set_workspace", handle, C.c_void_p(self.buf.data_ptr()), need, _stream_ptr(stream))
 
 
@@ -213,7 +223,8 @@ class Plan:
         """nsteps sweeps; `fields` is permuted in place like the pointer array.
         src_amp[t, s] is added at source s after step t, times src_scale[s]
         when given (device FP64).  A variant that needs a run workspace gets
-        one allocated here (caller memory kept with the plan)."""
+        one allocated here (caller memory kept with the plan); a large 2D wave
+        goes on without it, one step per launch, where the memory is short."""
         ptrs = (C.c_void_p * 3)(*[f.ptr for f in fields] + [0] * (3 - len(fields)))
         sp = _Points(src, src_amp, src_scale)
         rp = _Points(rec, rec_trace)
@@ -223,7 +234,7 @@ class Plan:
                 _check_f64_device(src_scale, (sp.n,), "src_scale")
         if rp.n:
             _check_f64_device(rec_trace, (nsteps, rp.n), "rec_trace")
-        self._ws.ensure(self._h, stream)
+        self._ws.ensure(self._h, stream, optional=self.ndim == 2)
         s, r = sp.source(), rp.receivers()
         call("stencil_run", self._h, ptrs, int(nsteps), C.byref(s) if s else None,
              C.byref(r) if r else None, _stream_ptr(stream))
@@ -269,7 +280,7 @@ class Plan:
         if len(rp):
             _check_f64_device(rec_trace, (nsteps, len(rp)), "rec_trace")
             r = ReceiversInterp(len(rp), rp.ctypes.data_as(C.c_void_p), C.c_void_p(rec_trace.data_ptr()))
-        self._ws.ensure(self._h, stream)
+        self._ws.ensure(self._h, stream, optional=self.ndim == 2)
         call("stencil_run_interp", self._h, ptrs, int(nsteps), C.byref(s) if s else None,
              C.byref(r) if r else None, _stream_ptr(stream))
         if ptrs[0] != fields[0].ptr:

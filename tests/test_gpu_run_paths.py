@@ -140,3 +140,24 @@ def test_heat_points_are_served_by_every_variant(device, shape, radius, noalloc)
         f = _fields(plan, 2)
         assert torch.equal(run(f, 0, n), rows), plan.variant_name(v)
         assert _same(f[:1], want[:1]), plan.variant_name(v)
+
+
+def test_a_large_2d_wave_runs_where_its_workspace_does_not_fit(device, monkeypatch):
+    import torch
+    plan, other = (S.Plan(S.WAVE2, (1000, 1003), 1, _weights(S.WAVE2, 1)) for _ in range(2))
+    f, want = _fields(plan, 3), _fields(plan, 3)
+    real = torch.empty
+
+    def empty(*size, **kw):
+        if size == (plan.run_workspace_bytes(),):
+            raise torch.cuda.OutOfMemoryError("out of memory")
+        return real(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    for _ in range(3):
+        plan.run(f, 16)
+    monkeypatch.undo()
+    for _ in range(3):
+        other.run(want, 16)
+    assert plan._ws.buf is None and other._ws.buf is not None
+    assert _same(f, want)

@@ -28,3 +28,25 @@ def test_host_runtime(stand_in, check):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_host_runtime.py"), stand_in, check], capture_output=True,
                        text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), (r.stdout + r.stderr)[-4000:]
+
+
+def test_a_short_memory_declines_only_an_optional_workspace(monkeypatch):
+    import torch
+
+    import paper_2404_02218_amd as S
+    asked = []
+
+    def empty(n, **kw):
+        asked.append(n)
+        raise torch.cuda.OutOfMemoryError("out of memory")
+
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    wave2d = S.Plan(S.WAVE2, (3000, 3013), 4, S.second_derivative_weights(8))
+    wave3d = S.Plan(S.WAVE2, (40, 44, 48), 4, S.second_derivative_weights(8))
+    wave3d.variant = 21   # two steps per pass, which needs its field pair
+    for _ in range(3):
+        wave2d._ws.ensure(wave2d.handle, optional=True)
+    assert asked == [wave2d.run_workspace_bytes()] and asked[0] > 0   # asked for once, then done without
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        wave3d._ws.ensure(wave3d.handle)
