@@ -602,10 +602,11 @@ int march_steps(int kind, int dtype, int radius, const Layout& L) {
     return pts >= four[dtype != STENCIL_F32][kind == STENCIL_WAVE2][radius - 1] ? 4 : 1;
 }
 
-// As host_points, with the lists by strip of the 2D sweep and by row, each
-// point under every strip whose stored points, widened by ext, hold it.
+// The lists by strip of the 2D sweep and by row, each point under every strip
+// whose stored points, widened by ext, hold it (the sweep reads no others).
 void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, HostPoints& H, int ext) {
-    host_points(L, n, pos, -1, H);
+    H = HostPoints{};
+    H.n = (int)n;
     H.tiled = true;
     const int W = march_width(radius), ns = std::max(1, (L.g.n[2] + W - 1) / W);
     std::vector<std::tuple<int, int, int>> order;   // (strip, y, index)
@@ -634,9 +635,11 @@ void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, Hos
 stencil_status upload_points(const HostPoints& H, int64_t n, int cfg, PointTables& T) {
     T.n = H.n;
     T.ngrp = H.ngrp;
-    ST_TRY(T.off.upload(H.off.data(), sizeof(int64_t) * (size_t)n));
-    ST_TRY(T.grp.upload(H.grp.data(), sizeof(int) * (size_t)n));
-    ST_TRY(T.gbeg.upload(H.gbeg.data(), sizeof(int) * H.gbeg.size()));
+    if (!H.off.empty()) {
+        ST_TRY(T.off.upload(H.off.data(), sizeof(int64_t) * (size_t)n));
+        ST_TRY(T.grp.upload(H.grp.data(), sizeof(int) * (size_t)n));
+        ST_TRY(T.gbeg.upload(H.gbeg.data(), sizeof(int) * H.gbeg.size()));
+    }
     if (H.tiled) {
         const int64_t m = H.tiles.back();
         ST_TRY(T.zyx4.upload(H.zyx4.data(), sizeof(int) * (size_t)(4 * m)));
@@ -829,6 +832,9 @@ struct RunLists {
     SrcList st, se;
     RecList rl;
     bool dense = false;   // 2D: too many sources in a row for passes of several steps
+    // strips and bricks: the sources (by position) and receivers have launches
+    // of their own, for lists whose tables by strip or tile have no room
+    bool apart = false;
 };
 
 RunLists plan_lists(stencil_plan p, const stencil_source* src, const stencil_receivers* rec) {
@@ -950,6 +956,14 @@ static hipError_t march_pass(const stencil_plan_s* p, int nt, const void* u, con
     return launch_march2d(mode, p->radius, p->dtype, nt, v, p->w, (int)row0, s);
 }
 
+// the sources and receivers of step t, behind the sweep that wrote `level`
+static hipError_t points_apart(const stencil_plan_s* p, void* level, const RunLists& RL, int64_t t, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (RL.st.n) e = launch_inject(p->dtype, level, p->L.g, RL.st, (int)t, s);
+    if (RL.rl.n && e == hipSuccess) e = launch_record(p->dtype, level, p->L.g, RL.rl, (int)t, s);
+    return e;
+}
+
 // 2D run by strips.  Passes of several steps read one buffer set and write
 // another: the two level buffers of a heat plan, the caller's pair and the
 // workspace pair (if one is attached) of a wave plan.  They come in even
@@ -960,7 +974,7 @@ static stencil_status enqueue_run_march2d(stencil_plan p, void* a, void* b, cons
     const Layout& L = p->L;
     const bool wave = p->kind == STENCIL_WAVE2;
     int64_t t = 0;
-    if (p->bc == STENCIL_BC_DIRICHLET0 && !RL.dense) {
+    if (p->bc == STENCIL_BC_DIRICHLET0 && !RL.dense && !RL.apart) {
         const size_t fb = (size_t)round_up(L.bytes, 256);
         void* const w0 = p->ws;
         void* const w1 = p->ws ? (char*)p->ws + fb : nullptr;
@@ -977,7 +991,8 @@ static stencil_status enqueue_run_march2d(stencil_plan p, void* a, void* b, cons
         void* const cur = ((t - done) & 1) ? b : a;
         void* const nxt = cur == a ? b : a;
         for (const CopyList& cl : per) HIP_TRY(launch_boxcopy(p->dtype, COPY_FIELD, cur, L.g, L.offset, cl, nullptr, s));
-        HIP_TRY(march_pass(p, 1, cur, nxt, beta, nxt, nullptr, cur, nxt, RL, t, s));
+        HIP_TRY(march_pass(p, 1, cur, nxt, beta, nxt, nullptr, cur, nxt, RL.apart ? RunLists{} : RL, t, s));
+        if (RL.apart) HIP_TRY(points_apart(p, nxt, RL, t, s));
     }
     return STENCIL_OK;
 }
@@ -1014,8 +1029,8 @@ stencil_status enqueue_run(stencil_plan p, Variant var, void* a, void* b, const 
     }
     const int mode = wave ? (p->damped ? MODE_WAVE_DAMP : MODE_WAVE) : MODE_HEAT;
     const float* damp = p->damped ? (const float*)p->damp.buf.p : nullptr;
-    const SrcList& sl = RL.st;
-    const RecList& rl = RL.rl;
+    const SrcList sl = RL.apart ? SrcList{} : RL.st;
+    const RecList rl = RL.apart ? RecList{} : RL.rl;
     std::vector<CopyList> per;
     if (p->bc == STENCIL_BC_PERIODIC) periodic_copies(L, p->radius, per);
     for (int64_t t = t0; t < nsteps; t++) {
@@ -1038,6 +1053,7 @@ stencil_status enqueue_run(stencil_plan p, Variant var, void* a, void* b, const 
             HIP_TRY(launch_zmarch(mode, p->radius, p->dtype, var.cfg, v, p->w, parity, (int)t, trow, s));
             // the z-marching heat kernels take no sources
             if (!wave && var.cfg != kBrickCfg && sl.n) HIP_TRY(launch_inject(p->dtype, nxt, L.g, sl, (int)t, s));
+            if (RL.apart) HIP_TRY(points_apart(p, nxt, RL, t, s));
         } else {
             ZView v{};
             v.u = cur;
@@ -1120,9 +1136,12 @@ struct ScratchPoints {
 };
 
 void place_points(ScratchCursor& c, const HostPoints& H, ScratchPoints& P) {
-    P.off = c.take(sizeof(int64_t) * H.off.size());
-    P.grp = c.take(sizeof(int) * H.grp.size());
-    P.gbeg = c.take(sizeof(int) * H.gbeg.size());
+    P = ScratchPoints{};
+    if (!H.off.empty()) {
+        P.off = c.take(sizeof(int64_t) * H.off.size());
+        P.grp = c.take(sizeof(int) * H.grp.size());
+        P.gbeg = c.take(sizeof(int) * H.gbeg.size());
+    }
     if (H.tiled) {
         P.zyx4 = c.take(sizeof(int) * H.zyx4.size());
         P.tiles = c.take(sizeof(int) * H.tiles.size());
@@ -1130,9 +1149,12 @@ void place_points(ScratchCursor& c, const HostPoints& H, ScratchPoints& P) {
 }
 
 hipError_t fill_points(const HostPoints& H, const ScratchPoints& P, hipStream_t s) {
-    hipError_t e = launch_fill_words(P.off, H.off.data(), sizeof(int64_t) * H.off.size(), s);
-    if (e == hipSuccess) e = launch_fill_words(P.grp, H.grp.data(), sizeof(int) * H.grp.size(), s);
-    if (e == hipSuccess) e = launch_fill_words(P.gbeg, H.gbeg.data(), sizeof(int) * H.gbeg.size(), s);
+    hipError_t e = hipSuccess;
+    if (!H.off.empty()) {
+        e = launch_fill_words(P.off, H.off.data(), sizeof(int64_t) * H.off.size(), s);
+        if (e == hipSuccess) e = launch_fill_words(P.grp, H.grp.data(), sizeof(int) * H.grp.size(), s);
+        if (e == hipSuccess) e = launch_fill_words(P.gbeg, H.gbeg.data(), sizeof(int) * H.gbeg.size(), s);
+    }
     if (e == hipSuccess && H.tiled) e = launch_fill_words(P.zyx4, H.zyx4.data(), sizeof(int) * H.zyx4.size(), s);
     if (e == hipSuccess && H.tiled) e = launch_fill_words(P.tiles, H.tiles.data(), sizeof(int) * H.tiles.size(), s);
     return e;
@@ -1519,9 +1541,8 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     const int cfg = (var.zmarch || var.tb) ? var.cfg : -1;
     const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
     HostPoints hs, he, hr;
-    const bool ext = var.tb || var.march2d;   // a second list of sources
+    bool ext = var.tb || var.march2d;   // a second list of sources
     if (var.march2d) {
-        host_points(L, 0, nullptr, -1, hs);
         host_strips(L, p->radius, ns, ns ? src->pos : nullptr, he, march_margin(p->radius));
         host_strips(L, p->radius, nr, nr ? rec->pos : nullptr, hr, 0);
     } else {
@@ -1531,12 +1552,25 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     }
     const bool scaled = ns > 0 && src->scale;
     // the regions this run needs, laid out from offset 0 first to size them
-    ScratchCursor sizing{0};
     ScratchPoints ps, pe, pr;
-    place_points(sizing, hs, ps);
-    if (ext) place_points(sizing, he, pe);
-    place_points(sizing, hr, pr);
-    if (scaled) sizing.take(sizeof(double) * (size_t)(nsteps * ns));
+    auto sized = [&]() {
+        ScratchCursor c{0};
+        place_points(c, hs, ps);
+        if (ext) place_points(c, he, pe);
+        place_points(c, hr, pr);
+        if (scaled) c.take(sizeof(double) * (size_t)(nsteps * ns));
+        return c;
+    };
+    ScratchCursor sizing = sized();
+    // the lists by strip or brick take up to twice the bytes of those by
+    // position: where they do not fit, the points get launches of their own
+    const bool apart = sizing.used > kNoAllocScratchBytes && (var.march2d || var.cfg == kBrickCfg);
+    if (apart) {
+        ext = false;
+        host_points(L, ns, ns ? src->pos : nullptr, -1, hs);
+        host_points(L, nr, nr ? rec->pos : nullptr, -1, hr);
+        sizing = sized();
+    }
     if (sizing.used > kNoAllocScratchBytes)
         return fail(STENCIL_E_NOMEM, "this run needs " + std::to_string(sizing.used) +
                                          " bytes of the static scratch; its maximum is " +
@@ -1560,6 +1594,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     }
     RunLists RL;
     RL.dense = he.dense;
+    RL.apart = apart;
     RL.st = scratch_src_list(hs, ps, amp);
     RL.se = ext ? scratch_src_list(he, pe, amp) : SrcList{};
     RL.rl.n = hr.n;

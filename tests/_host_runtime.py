@@ -224,6 +224,27 @@ def heat_points(h):
         assert seen > 0
 
 
+def long_lists_without_allocation(h):
+    """stencil_run_noalloc takes every list whose offsets and position groups (16 bytes a point) fit its 8 MiB,
+    at the sweeps by strips and bricks too, and refuses more."""
+    S = h.S
+    for kind, shape in ((S.WAVE2, (1100, 1000)), (S.HEAT, (1100, 1000)), (S.WAVE2, (110, 100, 100)),
+                        (S.HEAT, (110, 100, 100))):
+        w = S.heat_weights(4, 0.05) if kind == S.HEAT else S.second_derivative_weights(4)
+        plan = S.Plan(kind, shape, 2, w)
+        plan.variant = 0
+        f = h.fields(plan, 3 if kind == S.WAVE2 else 2)
+        for n, fits in ((1000, True), (300000, True), (522000, True), (1 << 20, False)):
+            pos = _points(h, shape, n)
+            for src, rec in ((S.Source(n, C.cast(pos, C.c_void_p), C.c_void_p(4096), None), None),
+                             (None, S.Receivers(n, C.cast(pos, C.c_void_p), C.c_void_p(8192)))):
+                st, _ = h.run(plan, f, 3, src=src, rec=rec, name="stencil_run_noalloc")
+                got = [x[0] for x in h.launches()]
+                assert (st == 0) == fits, (kind, shape, n, bool(src), st, h.lib.stencil_last_error())
+                if st == 0:
+                    assert sum("k_step2d" in x or "k_zbrick" in x for x in got) == 3
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")

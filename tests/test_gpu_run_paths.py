@@ -161,3 +161,35 @@ def test_a_large_2d_wave_runs_where_its_workspace_does_not_fit(device, monkeypat
         other.run(want, 16)
     assert plan._ws.buf is None and other._ws.buf is not None
     assert _same(f, want)
+
+
+@pytest.mark.parametrize("kind,shape,radius,dtype", [(S.WAVE2, (1000, 1003), 1, S.F32), (S.WAVE2, (700, 803), 4, S.F16),
+                                                     (S.HEAT, (1100, 1111), 2, S.F32), (S.WAVE2, (64, 80, 150), 4, S.F32),
+                                                     (S.HEAT, (64, 80, 150), 1, S.BF16)])
+@pytest.mark.parametrize("nsrc,nrec", [(10, 90), (40, 0), (300000, 70), (3, 400000)])
+def test_noalloc_equals_run_by_strips_and_bricks(device, kind, shape, radius, dtype, nsrc, nrec):
+    """Lists that the scratch array holds by strip or tile, with coincident sources and more than 16 in a row, and
+    lists (past 260,000 points) that it holds by position only."""
+    import torch
+    n, rng = 17, np.random.default_rng(6)
+    src = np.stack([rng.integers(0, k, nsrc) for k in shape], axis=1)
+    if nsrc == 40:
+        src[:, :-1], src[:, -1] = src[0, :-1], 300 % shape[-1] + np.arange(40) // 2
+    src[-1] = src[0]
+    rec = np.stack([rng.integers(0, k, nrec) for k in shape], axis=1) if nrec else None
+    amp = torch.from_numpy(rng.standard_normal((n, nsrc))).cuda()
+    plan = S.Plan(kind, shape, radius, _weights(kind, radius), dtype=dtype)
+    plan.variant = 0
+    plan._ws.ensure(plan.handle)
+    out = []
+    for name in ("stencil_run", "stencil_run_noalloc"):
+        f = _fields(plan, 8)
+        trace = torch.zeros((n, max(nrec, 1)), dtype=torch.float64, device=device)
+        sp, rp = S._Points(src, amp), S._Points(rec, trace)
+        r = rp.receivers()
+        ptrs = (C.c_void_p * 3)(*[x.ptr for x in f] + [0] * (3 - len(f)))
+        S.call(name, plan.handle, ptrs, n, C.byref(sp.source()), C.byref(r) if r else None, None)
+        torch.cuda.synchronize()
+        out.append((f, trace))
+    assert _same(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert nrec == 0 or float(out[0][1].abs().max()) > 0

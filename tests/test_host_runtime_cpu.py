@@ -23,7 +23,7 @@ def stand_in(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["shrunk_workspace", "concurrent_batch", "runs_that_are_not_repeated", "runs_in_a_caller_capture",
-                                   "heat_points"])
+                                   "heat_points", "long_lists_without_allocation"])
 def test_host_runtime(stand_in, check):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_host_runtime.py"), stand_in, check], capture_output=True,
                        text=True, timeout=300)
