@@ -58,6 +58,7 @@ struct Grid3 {
 // of source `index`.
 struct SrcList {
     int n;
+    int longest;          // most entries of a tile (bricks read up to 64 at once)
     const int* zyx4;
     const int* tile_begin;
     const int64_t* off;
@@ -248,7 +249,7 @@ bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz);
 // shot's receivers, shot -1 for padding
 inline constexpr int kBatchBrick = 2;
 hipError_t launch_brick_batch(int radius, int dtype, const ZView* d_views, const int* d_block_map, int nblocks,
-                              const Coefs& w, int parity, int arow, int trow, hipStream_t s);
+                              bool long_lists, const Coefs& w, int parity, int arow, int trow, hipStream_t s);
 // batched shots: d_block_map[2 b], d_block_map[2 b + 1] = shot and block within the shot of block b
 hipError_t launch_zmarch_batch(int radius, int dtype, int cfg, const ZView* d_views, const int* d_block_map,
                                int nblocks, const Coefs& w, int parity, int arow, int trow, hipStream_t s);

@@ -136,7 +136,7 @@ __global__ __launch_bounds__(64, 2) void k_march2d(M2View v, Coefs w, int row0) 
         const int sb = ld_inv(v.src.tile_begin + strip);
         src_end = ld_inv(v.src.tile_begin + strip + 1);
         for (int s = 0; s < NT && sb < src_end; s++) {
-            const int k = sb + rows_before(v.src.zyx4, sb, src_end, yb - (NT - 1 - s) * R);
+            const int k = first_from(v.src.zyx4, sb, src_end, 0, yb - (NT - 1 - s) * R);
             if (lane == s && k < src_end) {
                 ev_ptr = k;
                 ev_y = v.src.zyx4[4 * k + 1] + (s + 1) * R;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64, 2) void k_march2d(M2View v, Coefs w, int row0) 
         const int rb = ld_inv(v.rec.tile_begin + strip);
         rec_end = ld_inv(v.rec.tile_begin + strip + 1);
         if (rb < rec_end) {
-            const int k = rb + rows_before(v.rec.zyx4, rb, rec_end, yb);
+            const int k = first_from(v.rec.zyx4, rb, rec_end, 0, yb);
             if (lane >= 32 && lane < 32 + NT && k < rec_end && v.rec.zyx4[4 * k + 1] < ye) {
                 ev_ptr = k;
                 ev_y = v.rec.zyx4[4 * k + 1] + (lane - 31) * R;

@@ -256,9 +256,8 @@ void store_tune_choice(const std::string& full_key, const std::string& name) {
 struct PointTables {
     DevTable zyx4, tiles, off;
     DevTable grp, gbeg;           // entries grouped by position (point-kernel injection)
-    int n = 0, ngrp = 0;
+    int n = 0, ngrp = 0, longest = 0;
     int cfg = -1;
-    bool dense = false;
 };
 
 struct stencil_plan_s {
@@ -272,6 +271,7 @@ struct stencil_plan_s {
     int variant = 0;
     bool variant_forced = false;
     PointTables src, rec, adjrec;
+    bool points_apart = false;   // the last run's points have launches of their own
     PointTables src_ext;   // sources listed under every tile within R of them (temporal blocking)
     // caller memory attached by stencil_set_workspace: the second field pair
     // of the temporally blocked wave sweep (per shot for a batch), zero halos
@@ -525,27 +525,31 @@ void zyx_of(const Layout& L, const int64_t* p3, int out[3]) {
 // entries grouped by position (coincident entries are applied in index order
 // by one thread), and for cfg >= 0 the CSR over xy tiles of the z-marching
 // kernels, entries sorted by (tile, z).  ext > 0 lists a point under every
-// tile whose box widened by `ext` in x and y holds it.
+// tile whose box widened by `ext` in x and y holds it.  The groups are left out
+// on request: bricks do not read them.
 struct HostPoints {
-    int n = 0, ngrp = 0;
+    int n = 0, ngrp = 0, longest = 0;   // longest: most entries of a tile
     bool tiled = false;
-    bool dense = false;   // 2D strips: more than kMarchRowSources points in a row of a strip
+    bool dense = false;   // 2D strips: more than kMarchRowSources points in a row of one
     std::vector<int64_t> off;
     std::vector<int> grp, gbeg, zyx4, tiles;
 };
 
-void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPoints& H, int ext = 0) {
+void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPoints& H, int ext = 0,
+                 bool groups = true) {
     H = HostPoints{};
     H.n = (int)n;
     H.off.assign((size_t)std::max<int64_t>(n, 1), 0);
     for (int64_t i = 0; i < n; i++) H.off[i] = interior_offset(L, pos + 3 * i);
-    H.grp.assign((size_t)std::max<int64_t>(n, 1), 0);
-    H.gbeg.assign(1, 0);
-    for (int64_t i = 0; i < n; i++) H.grp[i] = (int)i;
-    std::stable_sort(H.grp.begin(), H.grp.begin() + n, [&](int a, int b) { return H.off[a] < H.off[b]; });
-    for (int64_t k = 1; k <= n; k++)
-        if (k == n || H.off[H.grp[k]] != H.off[H.grp[k - 1]]) H.gbeg.push_back((int)k);
-    H.ngrp = (int)H.gbeg.size() - 1;
+    if (groups) {
+        H.grp.assign((size_t)std::max<int64_t>(n, 1), 0);
+        H.gbeg.assign(1, 0);
+        for (int64_t i = 0; i < n; i++) H.grp[i] = (int)i;
+        std::stable_sort(H.grp.begin(), H.grp.begin() + n, [&](int a, int b) { return H.off[a] < H.off[b]; });
+        for (int64_t k = 1; k <= n; k++)
+            if (k == n || H.off[H.grp[k]] != H.off[H.grp[k - 1]]) H.gbeg.push_back((int)k);
+        H.ngrp = (int)H.gbeg.size() - 1;
+    }
     if (cfg < 0) return;
     H.tiled = true;
     const int TX = tile_tx(cfg), TY = tile_ty(cfg);
@@ -578,6 +582,7 @@ void host_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, HostPo
         H.zyx4[4 * k + 3] = i;
         H.tiles[std::get<0>(order[k]) + 1]++;
     }
+    H.longest = *std::max_element(H.tiles.begin(), H.tiles.end());
     for (size_t t = 1; t < H.tiles.size(); t++) H.tiles[t] += H.tiles[t - 1];
 }
 
@@ -604,17 +609,27 @@ int march_steps(int kind, int dtype, int radius, const Layout& L) {
 
 // The lists by strip of the 2D sweep and by row, each point under every strip
 // whose stored points, widened by ext, hold it (the sweep reads no others).
-void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, HostPoints& H, int ext) {
+// most > 0: more than that many in a row of a strip set H.dense and end here,
+// for the lists are of no use then.
+void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, HostPoints& H, int ext, int most = 0) {
     H = HostPoints{};
     H.n = (int)n;
     H.tiled = true;
     const int W = march_width(radius), ns = std::max(1, (L.g.n[2] + W - 1) / W);
     std::vector<std::tuple<int, int, int>> order;   // (strip, y, index)
+    // a long list is counted before it is sorted
+    std::vector<int> in_row(most > 0 && n > 4096 ? (size_t)ns * L.g.n[1] : 0, 0);
     for (int64_t i = 0; i < n; i++) {
         int zyx[3];
         zyx_of(L, pos + 3 * i, zyx);
         const int s0 = std::max(0, (zyx[2] - ext) / W), s1 = std::min(ns - 1, (zyx[2] + ext) / W);
-        for (int k = s0; k <= s1; k++) order.emplace_back(k, zyx[1], (int)i);
+        for (int k = s0; k <= s1; k++) {
+            if (!in_row.empty() && ++in_row[(size_t)k * L.g.n[1] + zyx[1]] > most) {
+                H.dense = true;
+                return;
+            }
+            order.emplace_back(k, zyx[1], (int)i);
+        }
     }
     std::stable_sort(order.begin(), order.end());
     H.zyx4.assign(std::max<size_t>(4 * order.size(), 4), 0);
@@ -624,8 +639,8 @@ void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, Hos
         zyx_of(L, pos + 3 * i, &H.zyx4[4 * k]);
         H.zyx4[4 * k + 3] = i;
         H.tiles[std::get<0>(order[k]) + 1]++;
-        const size_t back = kMarchRowSources;
-        H.dense |= k >= back && std::get<0>(order[k]) == std::get<0>(order[k - back]) &&
+        const size_t back = (size_t)most;
+        H.dense |= most > 0 && k >= back && std::get<0>(order[k]) == std::get<0>(order[k - back]) &&
                    std::get<1>(order[k]) == std::get<1>(order[k - back]);
     }
     for (size_t t = 1; t < H.tiles.size(); t++) H.tiles[t] += H.tiles[t - 1];
@@ -635,8 +650,9 @@ void host_strips(const Layout& L, int radius, int64_t n, const int64_t* pos, Hos
 stencil_status upload_points(const HostPoints& H, int64_t n, int cfg, PointTables& T) {
     T.n = H.n;
     T.ngrp = H.ngrp;
-    if (!H.off.empty()) {
-        ST_TRY(T.off.upload(H.off.data(), sizeof(int64_t) * (size_t)n));
+    T.longest = H.longest;
+    if (!H.off.empty()) ST_TRY(T.off.upload(H.off.data(), sizeof(int64_t) * (size_t)n));
+    if (!H.gbeg.empty()) {
         ST_TRY(T.grp.upload(H.grp.data(), sizeof(int) * (size_t)n));
         ST_TRY(T.gbeg.upload(H.gbeg.data(), sizeof(int) * H.gbeg.size()));
     }
@@ -646,20 +662,20 @@ stencil_status upload_points(const HostPoints& H, int64_t n, int cfg, PointTable
         ST_TRY(T.tiles.upload(H.tiles.data(), sizeof(int) * H.tiles.size()));
     }
     T.cfg = cfg;
-    T.dense = H.dense;
     return STENCIL_OK;
 }
 
 // Build the device tables of a point list.
 stencil_status build_points(const Layout& L, int64_t n, const int64_t* pos, int cfg, PointTables& T, int ext = 0) {
     HostPoints H;
-    host_points(L, n, pos, cfg, H, ext);
+    host_points(L, n, pos, cfg, H, ext, cfg != kBrickCfg);
     return upload_points(H, n, cfg, T);
 }
 
 SrcList src_list(const PointTables& T, const double* amp, const double* scale) {
     SrcList s{};
     s.n = T.n;
+    s.longest = T.longest;
     s.zyx4 = (const int*)T.zyx4.buf.p;
     s.tile_begin = (const int*)T.tiles.buf.p;
     s.off = (const int64_t*)T.off.buf.p;
@@ -831,9 +847,9 @@ void periodic_copies(const Layout& L, int radius, std::vector<CopyList>& out) {
 struct RunLists {
     SrcList st, se;
     RecList rl;
-    bool dense = false;   // 2D: too many sources in a row for passes of several steps
     // strips and bricks: the sources (by position) and receivers have launches
-    // of their own, for lists whose tables by strip or tile have no room
+    // of their own, where a strip has many sources in a row or the tables by
+    // strip or tile have no room
     bool apart = false;
 };
 
@@ -842,7 +858,7 @@ RunLists plan_lists(stencil_plan p, const stencil_source* src, const stencil_rec
     r.st = src_list(p->src, src ? src->amp : nullptr, nullptr);
     r.se = src_list(p->src_ext, src ? src->amp : nullptr, nullptr);
     r.rl = rec_list(p->rec, rec ? rec->trace : nullptr);
-    r.dense = p->src_ext.dense;
+    r.apart = p->points_apart;
     return r;
 }
 
@@ -974,7 +990,7 @@ static stencil_status enqueue_run_march2d(stencil_plan p, void* a, void* b, cons
     const Layout& L = p->L;
     const bool wave = p->kind == STENCIL_WAVE2;
     int64_t t = 0;
-    if (p->bc == STENCIL_BC_DIRICHLET0 && !RL.dense && !RL.apart) {
+    if (p->bc == STENCIL_BC_DIRICHLET0 && !RL.apart) {
         const size_t fb = (size_t)round_up(L.bytes, 256);
         void* const w0 = p->ws;
         void* const w1 = p->ws ? (char*)p->ws + fb : nullptr;
@@ -1163,6 +1179,7 @@ hipError_t fill_points(const HostPoints& H, const ScratchPoints& P, hipStream_t 
 SrcList scratch_src_list(const HostPoints& H, const ScratchPoints& P, const double* amp) {
     SrcList l{};
     l.n = H.n;
+    l.longest = H.longest;
     l.zyx4 = (const int*)P.zyx4;
     l.tile_begin = (const int*)P.tiles;
     l.off = (const int64_t*)P.off;
@@ -1318,11 +1335,20 @@ static stencil_status run_args(stencil_plan p, void** fields, int64_t nsteps, co
 
 static stencil_status prepare_points(stencil_plan p, const Variant& var, const stencil_source* src,
                                      const stencil_receivers* rec) {
+    p->points_apart = false;
     if (var.march2d) {
         HostPoints H;
         const int64_t ns = src ? src->n : 0, nr = rec ? rec->n : 0;
+        host_strips(p->L, p->radius, ns, ns ? src->pos : nullptr, H, march_margin(p->radius), kMarchRowSources);
+        // A wave adds its sources one after another, 0.3 us each: with a tenth of
+        // the points of 1000^2 as sources (22 a row of a strip) a step took 19 us,
+        // with a launch of their own 11
+        p->points_apart = H.dense;
+        if (H.dense) {
+            ST_TRY(build_points(p->L, ns, src->pos, -1, p->src));
+            return build_points(p->L, nr, nr ? rec->pos : nullptr, -1, p->rec);
+        }
         p->src.n = p->src.ngrp = 0;
-        host_strips(p->L, p->radius, ns, ns ? src->pos : nullptr, H, march_margin(p->radius));
         ST_TRY(upload_points(H, ns, -1, p->src_ext));
         host_strips(p->L, p->radius, nr, nr ? rec->pos : nullptr, H, 0);
         return upload_points(H, nr, -1, p->rec);
@@ -1515,7 +1541,8 @@ static stencil_status run_common(stencil_plan p, void** fields, int64_t nsteps, 
                                     (int64_t)p->ws_bytes,   // decides the 2D sweep's steps per pass
                                     p->src.n,
                                     p->src.ngrp,
-                                    (int64_t)p->src_ext.dense,
+                                    p->src.longest > 64,   // decides the bricks' kernel
+                                    (int64_t)p->points_apart,
                                     p->src_ext.n,
                                     p->rec.n,
                                     (int64_t)(uintptr_t)p->src.grp.buf.p,
@@ -1543,7 +1570,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     HostPoints hs, he, hr;
     bool ext = var.tb || var.march2d;   // a second list of sources
     if (var.march2d) {
-        host_strips(L, p->radius, ns, ns ? src->pos : nullptr, he, march_margin(p->radius));
+        host_strips(L, p->radius, ns, ns ? src->pos : nullptr, he, march_margin(p->radius), kMarchRowSources);
         host_strips(L, p->radius, nr, nr ? rec->pos : nullptr, hr, 0);
     } else {
         host_points(L, ns, ns ? src->pos : nullptr, cfg, hs);
@@ -1564,7 +1591,7 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
     ScratchCursor sizing = sized();
     // the lists by strip or brick take up to twice the bytes of those by
     // position: where they do not fit, the points get launches of their own
-    const bool apart = sizing.used > kNoAllocScratchBytes && (var.march2d || var.cfg == kBrickCfg);
+    const bool apart = he.dense || (sizing.used > kNoAllocScratchBytes && (var.march2d || var.cfg == kBrickCfg));
     if (apart) {
         ext = false;
         host_points(L, ns, ns ? src->pos : nullptr, -1, hs);
@@ -1593,7 +1620,6 @@ stencil_status stencil_run_noalloc(stencil_plan p, void** fields, int64_t nsteps
         amp = amounts;
     }
     RunLists RL;
-    RL.dense = he.dense;
     RL.apart = apart;
     RL.st = scratch_src_list(hs, ps, amp);
     RL.se = ext ? scratch_src_list(he, pe, amp) : SrcList{};
@@ -2368,11 +2394,13 @@ static stencil_status enqueue_batch(stencil_plan p, const std::vector<ZView>& vi
         }
         t0 = 2 * passes;
     }
+    bool long_lists = false;
+    for (const ZView& v : views) long_lists |= v.src.longest > 64;
     for (size_t g = 0; var.cfg == kBrickCfg && g + 1 < p->group_first.size(); g++) {
         const int at = p->group_first[g], n = p->group_first[g + 1] - at;
         for (int64_t t = 0; t < nsteps; t++)
             HIP_TRY(launch_brick_batch(p->radius, p->dtype, (const ZView*)p->views.buf.p,
-                                       (const int*)p->block_map.buf.p + 4 * (size_t)at, n, p->w, (int)(t & 1), (int)t,
+                                       (const int*)p->block_map.buf.p + 4 * (size_t)at, n, long_lists, p->w, (int)(t & 1), (int)t,
                                        (any_rec && t >= 1) ? (int)(t - 1) : -1, s));
         t0 = nsteps;
     }
@@ -2511,6 +2539,7 @@ static stencil_status batch_run_concurrent(stencil_plan p, void** fields, int64_
             key.push_back(q->variant);
             key.push_back(L.st.n);
             key.push_back(L.st.ngrp);
+            key.push_back(L.st.longest > 64);
             key.push_back(L.se.n);
             key.push_back(L.rl.n);
         }
@@ -2580,6 +2609,7 @@ stencil_status stencil_batch_run(stencil_plan p, void** fields, int64_t nsteps, 
             key.push_back((int64_t)(uintptr_t)v.src.amp);
             key.push_back((int64_t)(uintptr_t)v.rec.trace);
             key.push_back(v.src.n);
+            key.push_back(v.src.longest > 64);
             key.push_back(v.rec.n);
             key.push_back((int64_t)(uintptr_t)v.src.zyx4);
             key.push_back((int64_t)(uintptr_t)v.src.tile_begin);
@@ -3492,8 +3522,8 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
                 for (size_t g = 0; g + 1 < groups.size(); g++)
                     for (int k = 0; k < kBatchTuneSteps && e == hipSuccess; k++)
                         e = launch_brick_batch(p->radius, p->dtype, (const ZView*)vt.buf.p,
-                                               (const int*)bs.buf.p + 4 * (size_t)groups[g], groups[g + 1] - groups[g], p->w, 0, 0,
-                                               -1, s);
+                                               (const int*)bs.buf.p + 4 * (size_t)groups[g], groups[g + 1] - groups[g], false, p->w, 0,
+                                               0, -1, s);
                 return e;
             }
             if (p->batch)

@@ -61,14 +61,18 @@ __global__ __launch_bounds__(64 * kStepWaves) void k_step2d(M2View v, Coefs w, F
         for (int i = 0; i < 4; i++) dgx[i] = v.damp[v.g.n[0] + ny + min(max(x0 + i, 0), nx - 1)];
     }
     // The strip's sources and receivers, 64 at a time, one per lane, picked by
-    // row; the first ones are loaded here, so that their chains of loads (list,
-    // entry, amount) run beside the field's
+    // row (-1 before the wave's rows, -2 behind them); the first ones are loaded
+    // here, so that their chains of loads (list, entry, amount) run beside the
+    // field's.  Of a longer list the wave looks for its own rows next, behind the
+    // arithmetic, where it does not hold up the field's loads.  (It walked the
+    // whole list before: with 4096 receivers on 1000^2, FP32, r = 4, a step took
+    // 7.7 us, now 4.6.)
     int src_begin = 0, src_end = 0, src_row = -1, src_x = 0;
     double src_amt = 0.0;
     auto load_sources = [&](int from) {
         const int4 e = reinterpret_cast<const int4*>(v.src.zyx4)[min(from + lane, src_end - 1)];
         const bool in = from + lane < src_end && e.y >= yb && e.y < ye;
-        src_row = in ? e.y - yb : -1;
+        src_row = in ? e.y - yb : e.y < ye ? -1 : -2;
         src_x = e.z - X0;
         if (in) src_amt = v.src.amp[(int64_t)row0 * v.src.n + e.w] * (v.src.scale ? v.src.scale[e.w] : 1.0);
     };
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(64 * kStepWaves) void k_step2d(M2View v, Coefs w, F
     int rec_begin = 0, rec_end = 0, rec_row = -1, rec_x = 0, rec_at = 0;
     auto load_receivers = [&](int from) {
         const int4 e = reinterpret_cast<const int4*>(v.rec.zyx4)[min(from + lane, rec_end - 1)];
-        rec_row = from + lane < rec_end && e.y >= yb && e.y < ye ? e.y - yb : -1;
+        rec_row = from + lane < rec_end && e.y >= yb && e.y < ye ? e.y - yb : e.y < ye ? -1 : -2;
         rec_x = e.z - X0;
         rec_at = e.w;
     };
@@ -136,7 +140,14 @@ __global__ __launch_bounds__(64 * kStepWaves) void k_step2d(M2View v, Coefs w, F
                 o[r][i] = time_update<MODE>(acc, c[i], comp(p4, i), comp(b4, i));
         }
     }
-    for (int from = src_begin; from < src_end; from += 64) {
+    // the next entries of a list, or `end`
+    auto next = [&](const int* zyx4, int from, int end, int last_row) {
+        if (from + 64 >= end || last_row == -2) return end;
+        int stop = end;
+        return near_first(zyx4, from + 64, stop, 0, yb);
+    };
+    for (int from = src_begin; from < src_end;
+         from = next(v.src.zyx4, from, src_end, __builtin_amdgcn_readlane(src_row, 63))) {
         if (from > src_begin) load_sources(from);
         const int lo = __double2loint(src_amt), hi = __double2hiint(src_amt);
         for (uint64_t mine = __ballot(src_row >= 0); mine; mine &= mine - 1) {   // in the list's order
@@ -153,7 +164,8 @@ __global__ __launch_bounds__(64 * kStepWaves) void k_step2d(M2View v, Coefs w, F
         }
     }
     bool put = false;
-    for (int from = rec_begin; from < rec_end; from += 64) {
+    for (int from = rec_begin; from < rec_end;
+         from = next(v.rec.zyx4, from, rec_end, __builtin_amdgcn_readlane(rec_row, 63))) {
         if (from > rec_begin) load_receivers(from);
         if (!__ballot(rec_row >= 0)) continue;
         if (!put) {

@@ -21,14 +21,32 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// entries of a row-sorted list [from, end) above row y, counted by the wave
-__device__ __forceinline__ int rows_before(const int* zyx4, int from, int end, int y) {
-    int n = 0;
-    for (int e0 = from; e0 < end; e0 += 64) {
-        const int e = e0 + ((int)threadIdx.x & 63);
-        n += __popcll(__ballot(e < end && zyx4[4 * e + 1] < y));
+// Searches of a sorted list's range [from, end) by the whole wave for the first
+// entry that does not lie before (z, y): lists by strip are sorted by y (z is 0
+// there), lists by tile by z and then y.  64 entries evenly apart narrow the
+// range 64 times a round.
+__device__ __forceinline__ int entries_before(const int* zyx4, int e, int end, int z, int y) {
+    const int4 q = reinterpret_cast<const int4*>(zyx4)[min(e, end - 1)];
+    return __popcll(__ballot(e < end && (q.x < z || (q.x == z && q.y < y))));
+}
+// an entry at or less than 64 in front of it (no load for up to 64 entries)
+__device__ __forceinline__ int near_first(const int* zyx4, int from, int& end, int z, int y) {
+    while (end - from > 64) {
+        const int step = (end - from + 63) >> 6;
+        const int n = entries_before(zyx4, from + ((int)threadIdx.x & 63) * step, end, z, y);
+        if (n == 0) {
+            end = from;
+        } else {
+            end = min(end, from + n * step);
+            from += (n - 1) * step + 1;
+        }
     }
-    return n;
+    return from;
+}
+// the entry itself, or `end`
+__device__ __forceinline__ int first_from(const int* zyx4, int from, int end, int z, int y) {
+    from = near_first(zyx4, from, end, z, y);
+    return from < end ? from + entries_before(zyx4, from + ((int)threadIdx.x & 63), end, z, y) : from;
 }
 
 }  // namespace stn

@@ -59,7 +59,12 @@ template <int MODE, int BZ>
 inline constexpr int kBrickWaves = BZ == 2 ? (kAdj<MODE> ? 4 : 5) : kAdj<MODE> ? 3 : 4;
 
 // One workgroup's brick: tile (tile_x, tile_y) and z-chunk zch of the box.
-template <int MODE, int R, typename T, int BZ>
+// LONG: a tile may have more than 64 sources.  Such a brick finds the entries of
+// its planes by a search and each wave those of its rows; where every brick of
+// the column walked the whole list, a gradient of 128^3 with 16384 receivers in
+// a plane took 92 us a step, now 64.  A form of its own, because the shorter
+// one loses 1% with the search in it.
+template <int MODE, int R, typename T, int BZ, bool LONG>
 __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3& box, int tile_x, int tile_y, int zch,
                                       int parity, int arow, float* __restrict__ lds) {
     using Z = ZBrick<R, BZ>;
@@ -163,6 +168,10 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
         const int tile = tile_y * v.ntx + tile_x;
         src_begin = ld_inv(v.src.tile_begin + tile);
         src_end = ld_inv(v.src.tile_begin + tile + 1);
+        if constexpr (LONG) {   // the brick's own planes
+            src_begin = first_from(v.src.zyx4, src_begin, src_end, zb, INT_MIN);
+            src_end = first_from(v.src.zyx4, src_begin, src_end, ze, INT_MIN);
+        }
         if (src_begin < src_end) load_sources(src_begin);
     }
 
@@ -239,17 +248,30 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
                 *reinterpret_cast<float4*>(own + p * PLANE) = make_float4(val[p][0], val[p][1], val[p][2], val[p][3]);
             wave_lds_fence();
             const int row0 = __builtin_amdgcn_readfirstlane(ty);
-            for (int from = src_begin; from < src_end; from += 64) {
-                if (chunks > 64) load_sources(from);
-                const int row = src_at % PLANE / LDX - R - row0;
-                const uint64_t mine = __ballot(src_at >= 0 && row >= 0 && row < 4);
-                const uint64_t next = __ballot(__shfl_up(src_at, 1) == src_at) & ~1ull;   // same point as the one before
-                for (uint64_t todo = mine; todo;) {
-                    const uint64_t go = todo & ~(next & (todo << 1));
-                    if (go >> (tid & 63) & 1) lds[src_at] = add(lds[src_at], src_amt);
-                    wave_lds_fence();
-                    todo &= ~go;
+            auto add_from = [&](int begin) __attribute__((always_inline)) {
+                for (int from = begin; from < src_end; from += 64) {
+                    if (chunks > 64) load_sources(from);
+                    const int row = src_at % PLANE / LDX - R - row0;
+                    const uint64_t mine = __ballot(src_at >= 0 && row >= 0 && row < 4);
+                    const uint64_t next = __ballot(__shfl_up(src_at, 1) == src_at) & ~1ull;   // same point as the one before
+                    for (uint64_t todo = mine; todo;) {
+                        const uint64_t go = todo & ~(next & (todo << 1));
+                        if (go >> (tid & 63) & 1) lds[src_at] = add(lds[src_at], src_amt);
+                        wave_lds_fence();
+                        todo &= ~go;
+                    }
                 }
+            };
+            if (!LONG || chunks <= 64) {
+                add_from(src_begin);
+            } else {   // the wave's own rows of each plane
+                const int end = src_end;
+                for (int z = zb, at = src_begin; z < ze; z++, at = src_end) {
+                    at = first_from(v.src.zyx4, at, end, z, Y0 + row0);
+                    src_end = first_from(v.src.zyx4, at, end, z, Y0 + row0 + 4);
+                    add_from(at);
+                }
+                src_end = end;
             }
 #pragma unroll
             for (int p = 0; p < BZ; p++) {
@@ -312,23 +334,25 @@ __device__ __forceinline__ void brick(const ZView& v, const Coefs& w, const Box3
 }
 
 // Receivers sample the input level of a launch (nothing writes it there).  They
-// have a workgroup of their own: in front of a brick their two dependent
-// loads would make that brick the last to end.
+// have workgroups of their own, in front of the bricks, one for 1024 of them:
+// within a brick their two dependent loads would make that brick the last to
+// end.  Workgroup k of n takes every nth 256 of them.
+__host__ __device__ inline int record_groups(int n) { return (n + 1023) / 1024; }
 template <typename T>
-__device__ __forceinline__ void record_input(const ZView& v, int parity, int trow) {
+__device__ __forceinline__ void record_input(const ZView& v, int parity, int trow, int k, int n) {
     const T* U = (const T*)(parity ? v.prev : v.u) + v.g.origin;
     double* trace = v.rec.trace + (int64_t)trow * v.rec.n;
-    for (int r = threadIdx.x; r < v.rec.n; r += 256) trace[r] = (double)Storage<T>::load(U + v.rec.off[r]);
+    for (int r = 256 * k + (int)threadIdx.x; r < v.rec.n; r += 256 * n) trace[r] = (double)Storage<T>::load(U + v.rec.off[r]);
 }
 
-// The launch's grid: bricks numbered x, y, z or (zfast) z, x, y, one workgroup
-// more in front if receivers are recorded.
+// The launch's grid: the workgroups that record receivers, in front, and nb
+// bricks numbered x, y, z or (zfast) z, x, y.
 struct BrickGrid {
     int nb, zfast;
     FastDiv inner, row;   // by the bricks of an xy plane (zfast: of a column); by v.ntx
 };
 
-template <int MODE, int R, typename T, int BZ>
+template <int MODE, int R, typename T, int BZ, bool LONG>
 __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v, Coefs w, Box3 box, BrickGrid grid,
                                                                        int parity, int arow, int trow) {
     __shared__ __attribute__((aligned(16))) float lds[BZ * ZBrick<R, BZ>::PLANE];
@@ -337,17 +361,26 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
     // compiler leaves for later then find them in the scalar cache
     asm volatile("" ::"s"(v.u), "s"(v.g.s[0]), "s"(v.src.n), "s"(v.ntx), "s"(box.lo[1]), "s"(v.rec.n), "s"(w.cd0), "s"(grid.nb));
     if (trow >= 0) {
-        if (b == 0) {
-            record_input<T>(v, parity, trow);
-            return;
+        if constexpr (LONG) {
+            const int nrec = record_groups(v.rec.n);
+            if (b < nrec) {
+                record_input<T>(v, parity, trow, b, nrec);
+                return;
+            }
+            b -= nrec;
+        } else {
+            if (b == 0) {
+                record_input<T>(v, parity, trow, 0, 1);
+                return;
+            }
+            b--;
         }
-        b--;
     }
     const int lb = xcd_remap(b, grid.nb);
     const int q = (int)fdiv((uint32_t)lb, grid.inner), r = lb - q * (int)grid.inner.d;
     const int tile = grid.zfast ? q : r, zch = grid.zfast ? r : q;
     const int tile_y = (int)fdiv((uint32_t)tile, grid.row);
-    brick<MODE, R, T, BZ>(v, w, box, tile - tile_y * (int)grid.row.d, tile_y, zch, parity, arow, lds);
+    brick<MODE, R, T, BZ, LONG>(v, w, box, tile - tile_y * (int)grid.row.d, tile_y, zch, parity, arow, lds);
 }
 
 // The bricks of a group of shots in one launch: block_map[b] = (shot, tile x,
@@ -355,7 +388,7 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE, BZ>)) void k_zbrick(ZView v
 // XCD.  A shot
 // of 100^3 has too few bricks to fill the chip and takes 6 us for 2.8 TB/s; all
 // shots together fill it.
-template <typename T>
+template <typename T, bool LONG>
 __global__ __launch_bounds__(256, (kBrickWaves<MODE_WAVE, kBatchBrick>)) void k_zbrick_batch(
     const ZView* __restrict__ views, const int4* __restrict__ block_map, Coefs w, int parity, int arow, int trow) {
     __shared__ __attribute__((aligned(16))) float lds[kBatchBrick * ZBrick<4, kBatchBrick>::PLANE];
@@ -377,18 +410,18 @@ __global__ __launch_bounds__(256, (kBrickWaves<MODE_WAVE, kBatchBrick>)) void k_
     v.rec.trace = ld_inv(&from->rec.trace);
     Box3 box{};
     for (int a = 0; a < 3; a++) box.n[a] = v.g.n[a];
-    brick<MODE_WAVE, 4, T, kBatchBrick>(v, w, box, e.y, e.z, e.w, parity, arow, lds);
+    brick<MODE_WAVE, 4, T, kBatchBrick, LONG>(v, w, box, e.y, e.z, e.w, parity, arow, lds);
     // (a workgroup in front for this, as in k_zbrick, costs 4% here: it moves
     // the bricks of one XCD against those of the others)
-    if (trow >= 0 && (e.y | e.z | e.w) == 0) record_input<T>(v, parity, trow);
+    if (trow >= 0 && (e.y | e.z | e.w) == 0) record_input<T>(v, parity, trow, 0, 1);
 }
 
 template <typename T>
-hipError_t brick_batch(const ZView* views, const int* block_map, int nblocks, const Coefs& w, int parity, int arow,
-                       int trow, hipStream_t s) {
+hipError_t brick_batch(const ZView* views, const int* block_map, int nblocks, bool long_lists, const Coefs& w,
+                       int parity, int arow, int trow, hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zbrick_batch<T>, dim3((unsigned)nblocks), dim3(256), 0, s, views, (const int4*)block_map, w,
-                       parity, arow, trow);
+    auto k = long_lists ? k_zbrick_batch<T, true> : k_zbrick_batch<T, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(256), 0, s, views, (const int4*)block_map, w, parity, arow, trow);
     return hipGetLastError();
 }
 
@@ -400,12 +433,13 @@ hipError_t brick_launch(const ZView& v, const Coefs& w, const Box3& box, int par
     b.nzc = (int)((box.n[0] + BZ - 1) / BZ);
     const int64_t nb = (int64_t)b.ntx * b.nty * b.nzc;
     if (nb == 0) return hipSuccess;
-    if (nb >= INT_MAX) return hipErrorInvalidConfiguration;
     if (v.rec.n == 0) trow = -1;
+    const int nrec = trow >= 0 ? record_groups(v.rec.n) : 0;
+    if (nb >= INT_MAX - nrec) return hipErrorInvalidConfiguration;
     const bool zfast = brick_zfast(box.n, R, sizeof(T), BZ);
     const BrickGrid grid{(int)nb, zfast, fast_div((uint32_t)(zfast ? b.nzc : b.ntx * b.nty)), fast_div((uint32_t)b.ntx)};
-    hipLaunchKernelGGL((k_zbrick<MODE, R, T, BZ>), dim3((unsigned)(nb + (trow >= 0))), dim3(256), 0, s, b, w, box, grid,
-                       parity, arow, trow);
+    auto k = v.src.longest > 64 || nrec > 1 ? k_zbrick<MODE, R, T, BZ, true> : k_zbrick<MODE, R, T, BZ, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(nb + nrec)), dim3(256), 0, s, b, w, box, grid, parity, arow, trow);
     return hipGetLastError();
 }
 
@@ -447,12 +481,12 @@ hipError_t brick_m(int mode, int radius, int bz, const ZView& v, const Coefs& w,
 }  // namespace
 
 hipError_t launch_brick_batch(int radius, int dtype, const ZView* views, const int* block_map, int nblocks,
-                              const Coefs& w, int parity, int arow, int trow, hipStream_t s) {
+                              bool long_lists, const Coefs& w, int parity, int arow, int trow, hipStream_t s) {
     if (radius != 4) return hipErrorInvalidValue;
     switch (dtype) {
-        case DT_F32: return brick_batch<float>(views, block_map, nblocks, w, parity, arow, trow, s);
-        case DT_BF16: return brick_batch<bf16>(views, block_map, nblocks, w, parity, arow, trow, s);
-        case DT_F16: return brick_batch<f16>(views, block_map, nblocks, w, parity, arow, trow, s);
+        case DT_F32: return brick_batch<float>(views, block_map, nblocks, long_lists, w, parity, arow, trow, s);
+        case DT_BF16: return brick_batch<bf16>(views, block_map, nblocks, long_lists, w, parity, arow, trow, s);
+        case DT_F16: return brick_batch<f16>(views, block_map, nblocks, long_lists, w, parity, arow, trow, s);
     }
     return hipErrorInvalidValue;
 }

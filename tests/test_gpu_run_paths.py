@@ -193,3 +193,121 @@ def test_noalloc_equals_run_by_strips_and_bricks(device, kind, shape, radius, dt
         out.append((f, trace))
     assert _same(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert nrec == 0 or float(out[0][1].abs().max()) > 0
+
+
+def _ab(plan, n, a, b, **points):
+    """The fields and the trace of a run at variant a (or of single steps for None) and at variant b."""
+    import torch
+    out = []
+    for v in (a, b):
+        plan.variant = 0 if v is None else v
+        f = _fields(plan, 9)
+        rec, amp = points.get("rec"), points.get("src_amp")
+        trace = torch.zeros((n, len(rec)), dtype=torch.float64, device="cuda") if rec is not None else None
+        for t0, k in [(t, 1) for t in range(n)] if v is None else [(0, n)]:
+            plan.run(f, k, src=points.get("src"), src_amp=amp[t0:t0 + k].contiguous() if amp is not None else None,
+                     rec=rec, rec_trace=trace[t0:t0 + k] if trace is not None else None)
+        out.append((f, trace))
+    return out
+
+
+@pytest.mark.parametrize("shape,dtype", [((9, 33, 130), S.F32), ((21, 16, 64), S.F32), ((40, 50, 70), S.BF16),
+                                         ((6, 531, 1101), S.F16)])
+@pytest.mark.parametrize("count", [64, 65, 700, 6000])
+def test_long_lists_in_bricks_equal_zmarch(device, shape, dtype, count):
+    """Lists past the 64 entries that a brick reads at once: spread, in one plane, in one column of bricks, with
+    coincident points; and as many receivers as several recording workgroups take."""
+    import torch
+    n, rng = 4, np.random.default_rng(count)
+    plan = S.Plan(S.WAVE2, shape, 4, _weights(S.WAVE2, 4), dtype=dtype)
+    spread = np.stack([rng.integers(0, k, count) for k in shape], axis=1)
+    plane, column = spread.copy(), spread.copy()
+    plane[:, 0] = shape[0] - 2
+    column[:, 1:] = np.minimum(column[:, 1:], 15)
+    amp = torch.from_numpy(rng.standard_normal((n, count))).cuda()
+    for src in (spread, plane, column):
+        src[count // 2] = src[0]
+        (f, tf), (g, tg) = _ab(plan, n, 0, 1, src=src, src_amp=amp, rec=spread)
+        assert _same(f, g) and torch.equal(tf, tg)
+
+
+def test_long_lists_in_the_gradient_equal_zmarch(device):
+    """A full surface of receivers, whose residuals are the adjoint's sources: 1024 in one plane of a brick."""
+    import torch
+    shape, n, every = (20, 37, 150), 7, 3
+    rng = np.random.default_rng(2)
+    surface = np.stack([a.ravel() for a in np.meshgrid([5], range(37), range(150), indexing="ij")], axis=1)
+    m = torch.from_numpy(1.0 / rng.uniform(1500, 4500, shape) ** 2).cuda()
+    wavelet = torch.from_numpy(rng.standard_normal((n, 1))).cuda()
+    d_obs = torch.from_numpy(rng.standard_normal((n, len(surface)))).cuda()
+    got = []
+    for variant in (0, 1):
+        plan = S.Plan(S.WAVE2, shape, 4, _weights(S.WAVE2, 4))
+        plan.variant = variant
+        f = [plan.field() for _ in range(3)]
+        ws = torch.empty(plan.adjoint_workspace_bytes(n, every), dtype=torch.uint8, device=device)
+        trace, misfit = torch.zeros_like(d_obs), torch.zeros(1, dtype=torch.float64, device=device)
+        grad = torch.zeros(shape, dtype=torch.float64, device=device)
+        plan.gradient(f, m, 1e-3, 10.0, n, every, ws, [[5, 9, 20]], wavelet, surface, trace, d_obs, misfit, grad)
+        got.append((trace, misfit, grad))
+    assert float(got[0][2].abs().max()) > 0
+    assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+@pytest.mark.parametrize("kind,shape,radius,dtype", [(S.WAVE2, (70, 500), 4, S.F32), (S.HEAT, (64, 1000), 1, S.F16),
+                                                     (S.WAVE2, (1000, 1003), 1, S.F32), (S.HEAT, (1200, 1001), 1, S.F32)])
+@pytest.mark.parametrize("nsrc,nrec", [(65, 64), (3000, 0), (12, 5000), (1, 70000)])
+def test_long_lists_in_strips_equal_single_entries(device, kind, shape, radius, dtype, nsrc, nrec):
+    """Long lists of a strip, in passes of several steps and in single steps, against points applied to the fields
+    after steps without them."""
+    import torch
+    n, rng = 17, np.random.default_rng(nsrc)
+    at = rng.choice(shape[0] * shape[1], size=nsrc, replace=False)
+    src = np.stack([at // shape[1], at % shape[1]], axis=1)
+    amp = torch.from_numpy(rng.standard_normal((n, nsrc))).cuda()
+    rec = np.stack([rng.integers(0, k, nrec) for k in shape], axis=1) if nrec else None
+    plan = S.Plan(kind, shape, radius, _weights(kind, radius), dtype=dtype)
+    (f, tf), (g, tg) = _ab(plan, n, None, 0, src=src, src_amp=amp, rec=rec)
+    assert _same(f, g) and (rec is None or torch.equal(tf, tg))
+    # the points applied to the fields after each step without them
+    h, want = _fields(plan, 9), []
+    inner = (slice(plan.halo, -plan.halo),) * 2
+    for t in range(3):
+        plan.run(h, 1)
+        level = h[0].view[inner]
+        y, x = (torch.from_numpy(src[:, d]).cuda() for d in range(2))
+        level[y, x] = (level[y, x].double() + amp[t]).to(level.dtype)
+        if rec is not None:
+            want.append(level[torch.from_numpy(rec[:, 0]).cuda(), torch.from_numpy(rec[:, 1]).cuda()].double())
+    k = _fields(plan, 9)
+    trace = torch.zeros((3, max(nrec, 1)), dtype=torch.float64, device=device)
+    plan.run(k, 3, src=src, src_amp=amp[:3].contiguous(), rec=rec, rec_trace=trace if nrec else None)
+    assert _same(h[:1], k[:1])
+    assert rec is None or torch.equal(torch.stack(want), trace)
+
+
+@pytest.mark.parametrize("shape,rec,bound", [((1000, 1000), "all", 100.0), ((48, 400, 500), "surface", 150.0)])
+def test_long_receiver_lists_are_not_walked_by_every_wave(device, shape, rec, bound):
+    """us a step, from the difference of 40 and 240 steps a call.  One thread per receiver takes 12 and 71 with the
+    sweep; every wave walking its strip's list took 940, one workgroup for all receivers 370."""
+    import time
+
+    import torch
+    at = [range(k) for k in shape] if rec == "all" else [[6], range(shape[1]), range(shape[2])]
+    at = np.stack([a.ravel() for a in np.meshgrid(*at, indexing="ij")], axis=1)
+    plan = S.Plan(S.WAVE2, shape, 4, _weights(S.WAVE2, 4))
+    plan.variant = 0
+    f, best = _fields(plan, 1), []
+    for n in (40, 240):
+        trace = torch.zeros((n, len(at)), dtype=torch.float64, device=device)
+        times = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            plan.run(f, n, rec=at, rec_trace=trace)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best.append(min(times))
+    us = (best[1] - best[0]) / 200 * 1e6
+    print(f"{us:.1f} us a step")
+    assert us < bound
