@@ -304,10 +304,10 @@ stencil_status stencil_batch_layout(stencil_plan batch, int shot, int64_t* exten
 /* nsteps sweeps of every shot (Section 6.1 wave sweep per shot, as in
  * stencil_run), captured into one HIP graph.  By variant:
  *   - fused (zmarch_*, tb2_*): one launch per step (two steps for the
- *     temporally blocked form) covers the tiles of all shots.
- *     zmarch_64x16_t256_zc32 stands for bricks of 64 x 16 x 2 points here:
- *     one launch per step covers a group of shots whose fields fit the last
- *     cache together, and each group takes all its steps before the next;
+ *     temporally blocked form) covers the tiles of all shots;
+ *   - bricks_64x16x2_t256 (the default while every shot is small): one launch
+ *     per step covers a group of shots whose fields fit the last cache
+ *     together, and each group takes all its steps before the next;
  *   - persistent_zmarch_*: one launch runs every step over per-XCD queues of
  *     the shots' tiles, with a grid barrier between steps.  Its grid is as
  *     many workgroups as the GPU holds at once; a barrier wait is bounded
@@ -596,7 +596,7 @@ stencil_status stencil_check(stencil_plan plan, void* const* fields, stencil_che
  * fastest per step of one launch (2D multi-step plans: per step of 96
  * steps captured in a graph, as runs execute them); the choice is cached per
  * (device architecture, kind, ndim, radius, halo, boundary, dtype, damping,
- * shapes, field bytes), as a variant name.  With STENCIL_TUNE_CACHE set to a
+ * shapes, field bytes, generation of the kernels), as a variant name.  With STENCIL_TUNE_CACHE set to a
  * file path the cache is read from that file on the first tuning of the
  * process and every new choice is appended to it ("<arch> <key> <name>" per
  * line); a cached name the plan does not offer is ignored and re-tuned.  With
@@ -620,7 +620,7 @@ stencil_status stencil_variant_name(stencil_plan plan, int variant, char* buf, s
 stencil_status stencil_get_variant(stencil_plan plan, int* variant);
 
 /* Select a variant (no passage of the paper: kernel choice); every variant
- * computes the same bits.  Batch plans take z-marching variants only. */
+ * computes the same bits.  Batch plans take variants 1 and up. */
 stencil_status stencil_set_variant(stencil_plan plan, int variant);
 
 /* Time the candidates and keep the fastest, as described above (no passage

@@ -173,10 +173,12 @@ constexpr int kNumZVariants = kNumTileCfgs * kNumZChunks;
 // batch plans: persistent launches on the 64 x 16 streaming tile, one per
 // z-chunk length
 constexpr int kNumPersistent = kNumZChunks;
-// The batch variant that runs every shot in bricks: it has the place and the
-// name of the plain 64 x 16 tile with 32-plane chunks, which no measured batch
-// picked (8 shots of 96^3 to 224^3: 203 us a step, 127 in bricks).
-constexpr int kBatchBrickVariant = 1 + (kNumZChunks - 1) * kNumTileCfgs + 3;
+// The batch variant that runs every shot in bricks.  It has the place of the
+// 64 x 32 tile with 8 points per lane and 256-plane chunks, which batches do not
+// offer: in 18 of them (16 shots of 48^3 to 72^3, 8 of 96^3 to 224^3, 2 of 512^3
+// and mixed ones, each storage type) it took 1.46 to 4.5 times as long as the
+// fastest z-marching variant, farthest of all from being picked.
+constexpr int kBatchBrickVariant = 1 + 2;
 // steps of one tuning launch of a persistent variant
 constexpr int kPersistentTuneSteps = 4;
 // steps per shot or group of a timed batch that runs its shots one after
@@ -3101,6 +3103,9 @@ stencil_status stencil_variant_name(stencil_plan p, int variant, char* buf, size
                                   std::to_string(32 * kProgTileY)
                             : (variant == 0 ? "program_rtc_" : variant == 1 ? "program_interp_" : "program_rtc_tight_") +
                                   tile;
+    } else if (batch_bricks(p, variant)) {
+        name = "bricks_" + std::to_string(kBrickTileX) + "x" + std::to_string(kBrickTileY) + "x" +
+               std::to_string(kBatchBrick) + "_t256";
     } else if (batch_concurrent(p, variant)) {
         name = "shots_concurrent_" + std::to_string(kBranches);
     } else if (batch_persistent(p, variant)) {
@@ -3142,6 +3147,10 @@ stencil_status stencil_set_variant(stencil_plan p, int variant) {
     return STENCIL_OK;
 }
 
+// Raised when a kernel behind a variant's name changes, or the set of variants:
+// choices saved before that are then not taken, but tuned again.
+constexpr int kTuneGeneration = 2;
+
 // Everything that decides which variants exist and how fast they run:
 // device architecture, plan kind, dimensions, radius, halo, boundary,
 // storage, damping and shapes (the field size also gates the temporally
@@ -3166,7 +3175,7 @@ static std::string tune_key(stencil_plan p) {
         for (int a = 0; a < 3; a++) k += ":" + std::to_string(p->L.g.n[a]);
         k += ":B" + std::to_string(p->L.bytes);
     }
-    return k;
+    return k + ":g" + std::to_string(kTuneGeneration);
 }
 
 // the plan's variant called `name`, or -1

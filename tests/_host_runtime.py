@@ -245,6 +245,47 @@ def long_lists_without_allocation(h):
                     assert sum("k_step2d" in x or "k_zbrick" in x for x in got) == 3
 
 
+def batch_variants(h):
+    """Each batch variant launches the kernel that it is called after; small batches start with the bricks."""
+    S = h.S
+    for sides, default in (([(20, 24, 28), (36, 40, 44)], "bricks_64x16x2_t256"),
+                           ([(20, 24, 28), (300, 300, 300)], "zmarch_64x32_t256_zc64")):
+        batch = S.BatchPlan(sides, 4, S.second_derivative_weights(8))
+        names = [batch.variant_name(v) for v in range(batch.variant_count())]
+        assert len(set(names)) == len(names) and batch.variant_name(batch.variant) == default
+        f = [h.take(layout.bytes) for layout in batch.layouts for _ in range(3)]
+        for v, name in list(enumerate(names))[1:]:
+            if name.startswith(("tb2_", "persistent_", "shots_")):
+                continue
+            batch.variant = v
+            h.launches()
+            assert _run_batch(h, batch, f, 2)[0] == 0
+            got = {x[0] for x in h.launches()}
+            assert len(got) == 1 and ("k_zbrick_batch" in got.pop()) == name.startswith("bricks_"), name
+
+
+def saved_choices(h):
+    """A choice that an earlier generation of kernels saved is tuned again; one of this generation is taken."""
+    S, path = h.S, os.environ["STENCIL_TUNE_CACHE"]
+
+    def tuned():
+        plan = S.Plan(S.WAVE2, (40, 44, 48), 4, S.second_derivative_weights(8))
+        f = h.fields(plan, 3)
+        assert h.lib.stencil_tune(plan.handle, (C.c_void_p * 3)(*f), 1, None) == 0
+        return plan.variant_name(plan.variant)
+
+    with open(path, "w") as out:
+        out.write("unknown b0:k1:d3:r4:h4:bc0:t0:damp0:40:44:48:B%d zmarch_64x32_t256_zc32\n" % S.Plan(
+            S.WAVE2, (40, 44, 48), 4, S.second_derivative_weights(8)).layout.bytes)
+    first = tuned()
+    assert first != "zmarch_64x32_t256_zc32"
+    with open(path) as lines:
+        arch, key, name = lines.read().splitlines()[-1].split()
+    assert name == first and ":g" in key
+    h.launches()
+    assert tuned() == first and not h.launches()   # taken without timing
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")

@@ -311,3 +311,30 @@ def test_long_receiver_lists_are_not_walked_by_every_wave(device, shape, rec, bo
     us = (best[1] - best[0]) / 200 * 1e6
     print(f"{us:.1f} us a step")
     assert us < bound
+
+
+@pytest.mark.parametrize("dtype", [S.F32, S.BF16])
+def test_a_batch_in_bricks_equals_the_zmarch(device, dtype):
+    """Several groups of shots, with receivers and a list of more than 64 sources in a tile."""
+    import torch
+    sides, n, rng = [(190, 190, 190), (24, 24, 24), (180, 190, 200), (17, 40, 70), (186, 186, 186)], 5, np.random.default_rng(3)
+    batch = S.BatchPlan(sides, 4, _weights(S.WAVE2, 4), dtype=dtype)
+    names = {batch.variant_name(v): v for v in range(1, batch.variant_count())}
+    srcs = [np.stack([rng.integers(0, k, 3 if i else 400) for k in s], axis=1) for i, s in enumerate(sides)]
+    srcs[0][:, 1:] %= 16
+    recs = [np.stack([rng.integers(0, k, 300) for k in s], axis=1) for s in sides]
+    amps = [torch.from_numpy(rng.standard_normal((n, len(s)))).cuda() for s in srcs]
+    got = []
+    for name in ("bricks_64x16x2_t256", "zmarch_64x16_t256_zc32"):
+        batch.variant = names[name]
+        g = torch.Generator(device="cuda").manual_seed(3)
+        f = [[batch.field(i) for _ in range(3)] for i in range(len(sides))]
+        for i, shot in enumerate(f):
+            for x in shot[:2]:
+                x.view[4:-4, 4:-4, 4:-4] = torch.randn(sides[i], generator=g, device="cuda").to(x.view.dtype)
+            shot[2].view.copy_(torch.rand(shot[2].view.shape, generator=g, device="cuda") * 0.05)
+        traces = [torch.zeros((n, 300), dtype=torch.float64, device=device) for _ in sides]
+        batch.run(f, n, srcs=srcs, src_amps=amps, recs=recs, rec_traces=traces)
+        got.append((f, traces))
+    for a, b, s, t in zip(got[0][0], got[1][0], got[0][1], got[1][1]):
+        assert _same(a, b) and torch.equal(s, t)
