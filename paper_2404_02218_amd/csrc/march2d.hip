@@ -341,16 +341,20 @@ __global__ __launch_bounds__(64, 2) void k_march2d(M2View v, Coefs w, int row0) 
     }
 }
 
-// waves of a pass one GPU holds at once
+// waves of a pass the current device holds at once, asked for once per device
 template <int MODE, int R, typename T, int NT>
 hipError_t m2_resident(int& waves) {
+    static std::atomic<int> known[64];   // 0: not yet
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (dev < 64 && (waves = known[dev].load()) > 0) return hipSuccess;
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_march2d<MODE, R, T, NT>), 64,
                                                          March2D<T, MODE, R, NT>::LDS_BYTES);
     waves = std::max(1, cus * per_cu);
+    if (e == hipSuccess && dev < 64) known[dev] = waves;
     return e;
 }
 
@@ -359,15 +363,16 @@ hipError_t m2_launch(const M2View& v, const Coefs& w, int row0, hipStream_t s) {
     constexpr size_t lds = March2D<T, MODE, R, NT>::LDS_BYTES;
     if (v.nstrips == 0 || v.g.n[1] == 0) return hipSuccess;
     auto k = k_march2d<MODE, R, T, NT>;
-    static const hipError_t attr = allow_lds(k, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k, lds, lds_on);
     if (attr != hipSuccess) return attr;
     // As many chunks of rows as the GPU holds waves: every wave then starts
     // at once and ends with the others, and the 2 R NT rows around a chunk
     // are computed as few times as that allows.  8192^2 FP32 wave, radius 4,
     // NT = 4, us a step: 149 rows (2035 of 2048 waves) 110, 200 rows 133, 99
     // rows 126, 75 rows 116, 50 rows 119.
-    static int waves = 0;
-    static const hipError_t known = m2_resident<MODE, R, T, NT>(waves);
+    int waves = 0;
+    const hipError_t known = m2_resident<MODE, R, T, NT>(waves);
     if (known != hipSuccess) return known;
     M2View u = v;
     u.rows = std::max(4, (v.g.n[1] + std::max(1, waves / v.nstrips) - 1) / std::max(1, waves / v.nstrips));

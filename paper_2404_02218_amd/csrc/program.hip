@@ -138,8 +138,9 @@ hipError_t launch_program(const ProgView& v, hipStream_t s) {
     const int64_t nb = (int64_t)v.ntx * v.nty * v.nzc;
     if (nb == 0) return hipSuccess;
     const size_t lds = program_lds_bytes(v.nin, v.rz, v.ry);
-    static const hipError_t attr = allow_lds(k_program, sizeof(float) * kProgMaxFields * (2 * kProgMaxR + 2) *
-                                                            (kProgTileY + 2 * kProgMaxR) * (kProgTileX + 8));
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k_program, sizeof(float) * kProgMaxFields * (2 * kProgMaxR + 2) *
+                                                     (kProgTileY + 2 * kProgMaxR) * (kProgTileX + 8), lds_on);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k_program, dim3((unsigned)nb), dim3(kProgThreads), lds, s, v);
     return hipGetLastError();

@@ -3,6 +3,7 @@
 // library builds in parallel.
 #pragma once
 
+#include <atomic>
 #include <climits>
 #include <type_traits>
 
@@ -899,12 +900,20 @@ __global__ __launch_bounds__(BX* BY) void k_zmarch_batch_persistent(const ZView*
     }
 }
 
-// dynamic LDS above 64 KiB must be enabled per kernel once
+// Dynamic LDS above 64 KiB must be enabled once per kernel and device; `done`
+// has a bit for each device where it is.
 template <typename K>
-static hipError_t allow_lds(K kernel, size_t bytes) {
+static hipError_t allow_lds(K kernel, size_t bytes, std::atomic<uint64_t>& done) {
     if (bytes <= 65536) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)bytes);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+    if (done.load() & bit) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)bytes);
+    if (e == hipSuccess) done |= bit;
+    return e;
 }
 
 template <int MODE, int R, typename T, int C>
@@ -914,7 +923,8 @@ static hipError_t zm_launch(const ZView& v, const Coefs& w, int parity, int arow
     const int64_t nb = zmarch_blocks(v);
     if (nb == 0) return hipSuccess;
     auto k = k_zmarch<MODE, R, T, c.bx, c.by, c.vy, c.vx, c.nt>;
-    static const hipError_t attr = allow_lds(k, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k, lds, lds_on);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(c.bx * c.by), lds, s, v, w, parity, arow, trow);
     return hipGetLastError();
@@ -951,7 +961,8 @@ static hipError_t zb_launch(const ZView* views, const int* bmap, int nblocks, co
     constexpr size_t lds = sizeof(LdsT<T, c.vx>) * ZTile<R, c.bx, c.by, c.vy, c.vx>::LDS_FLOATS;
     if (nblocks == 0) return hipSuccess;
     auto k = k_zmarch_batch<R, T, c.bx, c.by, c.vy, c.vx, c.nt>;
-    static const hipError_t attr = allow_lds(k, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k, lds, lds_on);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(c.bx * c.by), lds, s, views, bmap, w, parity, arow, trow);
     return hipGetLastError();
@@ -979,7 +990,8 @@ static hipError_t zbp_kernel(int radius, int cfg, const void*& k, size_t& lds, i
     lds = sizeof(LdsT<T, c.vx>) * ZTile<4, c.bx, c.by, c.vy, c.vx>::LDS_FLOATS;
     threads = c.bx * c.by;
     auto kf = k_zmarch_batch_persistent<4, T, c.bx, c.by, c.vy, c.vx, c.nt>;
-    static const hipError_t attr = allow_lds(kf, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(kf, lds, lds_on);
     if (attr != hipSuccess) return attr;
     k = reinterpret_cast<const void*>(kf);
     return hipSuccess;

@@ -524,7 +524,8 @@ static hipError_t tb2_batch_launch(const TBView* views, const int* bmap, int nbl
     constexpr size_t lds = sizeof(float) * TB2<4, true>::LDS_FLOATS;
     if (nblocks == 0) return hipSuccess;
     auto k = k_tb2_batch<T>;
-    static const hipError_t attr = allow_lds(k, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k, lds, lds_on);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(kTB2Threads), lds, s, views, bmap, w, arow, trow_u, trow_p);
     return hipGetLastError();
@@ -536,7 +537,8 @@ static hipError_t tb2_launch(const TBView& v, const Coefs& w, int arow, int trow
     const int64_t nb = (int64_t)v.ntx * v.nty * v.nzc;
     if (nb == 0) return hipSuccess;
     auto k = k_tb2<MODE, R, T>;
-    static const hipError_t attr = allow_lds(k, lds);
+    static std::atomic<uint64_t> lds_on{0};
+    const hipError_t attr = allow_lds(k, lds, lds_on);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(kTB2Threads), lds, s, v, w, arow, trow_u, trow_p);
     return hipGetLastError();

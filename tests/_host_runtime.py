@@ -286,6 +286,29 @@ def saved_choices(h):
     assert tuned() == first and not h.launches()   # taken without timing
 
 
+def a_second_device(h):
+    """What is asked of the device once (large LDS, the waves it holds) is asked on each device."""
+    S = h.S
+    grids = []
+    for device in (0, 1, 0):
+        h.hip.stand_in_device(device)
+        plan = S.Plan(S.WAVE2, (40, 44, 48), 4, S.second_derivative_weights(8))
+        f, need = h.fields(plan, 3), 0
+        for v in range(plan.variant_count()):
+            plan.variant = v
+            need = plan.run_workspace_bytes()
+            if need:
+                S.call("stencil_set_workspace", plan.handle, C.c_void_p(h.take(need)), need, None)
+            assert h.run(plan, f, 8)[0] == 0
+        heat = S.Plan(S.HEAT, (8192, 8192), 4, S.heat_weights(8, 0.05))
+        h.launches()
+        assert h.run(heat, h.fields(heat, 2), 8)[0] == 0
+        swept = [x for x in h.launches() if "k_march2d" in x[0]]
+        assert swept
+        grids.append(swept[0][1])
+    assert grids[1] < grids[0] == grids[2]   # fewer waves at once: longer chunks of rows
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](Host(sys.argv[1]))
     print("ok")

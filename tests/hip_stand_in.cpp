@@ -50,6 +50,8 @@ std::set<Graph*> graphs, execs;
 std::map<void*, Capture*> capturing;   // stream -> capture
 int begun = 0, instantiated = 0, replayed = 0, syncs = 0;
 std::string failing;   // the call that returns an error, once
+int device = 0;        // the current device
+std::set<std::pair<const void*, int>> large_lds;   // kernels allowed more than 64 KiB of LDS, by device
 
 struct Config {
     Dim3 grid, block;
@@ -112,9 +114,10 @@ API int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void*
     configs.pop_back();
     return 0;
 }
-API int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t, void* stream) {
+API int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t shared, void* stream) {
     check_stream(stream);
     if (!kernels.count(f)) die("a kernel that was not registered");
+    if (shared > 65536 && !large_lds.count({f, device})) die("more than 64 KiB of LDS, not enabled on this device");
     if (fails("hipLaunchKernel")) return 1;
     Launch l{kernels[f], grid, block, stream, {}};
     for (const char* swept : {"k_step2d", "k_march2d", "k_zbrickI", "k_zmarchI"})
@@ -129,7 +132,7 @@ API int hipModuleLaunchKernel(void*, unsigned, unsigned, unsigned, unsigned, uns
 API int hipGetLastError() { return 0; }
 API const char* hipGetErrorString(int) { return "stand-in error"; }
 API int hipGetDevice(int* d) {
-    *d = 0;
+    *d = device;
     return 0;
 }
 API int hipDeviceGetAttribute(int* v, int, int) {
@@ -137,9 +140,12 @@ API int hipDeviceGetAttribute(int* v, int, int) {
     return 0;
 }
 API int hipGetDevicePropertiesR0600(void*, int) { return 1; }
-API int hipFuncSetAttribute(const void*, int, int) { return 0; }
+API int hipFuncSetAttribute(const void* f, int, int) {
+    large_lds.insert({f, device});
+    return 0;
+}
 API int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
-    *n = 8;
+    *n = 8 >> device;   // a device holds half as many as the one before
     return 0;
 }
 API int hipDeviceSynchronize() {
@@ -310,6 +316,7 @@ API int stand_in_launches() { return (int)noted.size(); }
 API const char* stand_in_name(int i) { return noted[(size_t)i].name.c_str(); }
 API const void* stand_in_arg0(int i) { return noted[(size_t)i].arg0; }
 API unsigned stand_in_grid(int i) { return noted[(size_t)i].grid.x; }
+API void stand_in_device(int d) { device = d; }
 API void stand_in_clear() { noted.clear(); }
 API void stand_in_fail(const char* call) { failing = call; }
 // captures begun, graphs instantiated, graphs launched, synchronisations;
