@@ -242,6 +242,10 @@ hipError_t launch_brick(int mode, int radius, int dtype, int bz, const ZView& v,
 hipError_t launch_march2d(int mode, int radius, int dtype, int nt, const M2View& v, const Coefs& w, int row0,
                           hipStream_t s);
 hipError_t launch_step2d(int mode, int radius, int dtype, const M2View& v, const Coefs& w, int row0, hipStream_t s);
+// whether the three fields of a box of n points fit the last-level cache (256 MB)
+inline bool brick_cached(const int64_t* n, size_t esize) {
+    return 3.0 * (double)esize * (double)n[0] * (double)n[1] * (double)n[2] <= (double)(1 << 28);
+}
 // whether the bricks of a box of n points run z first
 bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz);
 // batched shots in bricks of kBatchBrick planes; d_block_map: (shot, tile x, tile

@@ -395,14 +395,24 @@ int variant_count_of(const stencil_plan_s* p) {
 }
 
 // Planes per brick of the brick kernel over a box of n points.  Two keep the
-// most workgroups in flight; four read a level 3 times instead of 5 (radius
-// 4), which wins once the box is larger than the caches (512^3 FP32: 566 us a
-// step with 2, 463 with 4; 256^3: 47 and 51), and for 16-bit storage, whose
-// loads are half as wide, once four workgroups share a compute unit (207 x
-// 301 x 259: 33.3 and 31.3 us; 128^3: 6.4 and 6.6).
-int brick_planes(const int64_t* n, int dtype) {
+// most workgroups in flight and take the fewest registers; four read a level
+// (4 + 2r) / 4 times instead of (2 + 2r) / 2.  That wins where the levels' own
+// traffic decides and four workgroups share a compute unit: for heat, which
+// reads nothing else, from radius 3 on in FP32 and always in 16 bits, for the
+// wave with radius 4 in 16 bits; else once the fields pass the last-level cache.
+// us a step with 2 / 4 planes: FP32 wave r = 4 256^3 47 / 51, 288^3 94 / 84, 512^3
+// 566 / 463; r = 2 256^3 39 / 42, 288^3 80 / 74.  FP32 heat r = 4 160^3 12.2 /
+// 11.2, 224^3 24 / 21; r = 3 21 / 20; r = 2 224^3 18.7 / 18.9, 320^3 78 / 73.  BF16
+// wave r = 4 128^3 6.2 / 6.5, 224^3 20.9 / 19.3, 320^3 55 / 46; r = 3 224^3 17.1 /
+// 18.0, 288^3 30.6 / 31.5, 320^3 45 / 43; r = 1 20.3 / 20.7 at 256^3.  BF16 heat r =
+// 1 160^3 6.5 / 6.0, r = 2 256^3 15.8 / 14.6, r = 3 14.3 / 14.7 at 224^3, 17.7 / 17.3
+// at 256^3.
+int brick_planes(const int64_t* n, int kind, int radius, int dtype) {
     const int64_t tiles = ((n[2] + kBrickTileX - 1) / kBrickTileX) * ((n[1] + kBrickTileY - 1) / kBrickTileY);
-    const bool many = dtype == STENCIL_F32 ? n[0] * n[1] * n[2] > (int64_t(1) << 25) : tiles * ((n[0] + 3) / 4) >= 1024;
+    const bool f32 = dtype == STENCIL_F32, level_bound = kind == STENCIL_HEAT ? !f32 || radius >= 3 : !f32 && radius == 4;
+    const bool many = level_bound ? tiles * ((n[0] + 3) / 4) >= 1024
+                      : f32       ? !brick_cached(n, (size_t)dtype_size(dtype))
+                                  : n[0] * n[1] * n[2] > 28000000;
     return many ? 4 : 2;
 }
 
@@ -426,7 +436,7 @@ Variant plan_variant(const stencil_plan_s* p, int v) {
         r.zmarch = true;
         r.cfg = kBrickCfg;
         const int64_t n[3] = {p->L.g.n[0], p->L.g.n[1], p->L.g.n[2]};
-        r.zc = brick_planes(n, p->dtype);
+        r.zc = brick_planes(n, p->kind, p->radius, p->dtype);
         return r;
     }
     if (!p->batch && !p->program && p->ndim == 2 && v == 0) {
@@ -596,14 +606,22 @@ int march_width(int radius) { return 256 - 2 * march_margin(radius); }
 // Steps per pass of the 2D sweep: one, unless the grid is so large that the
 // memory traffic a deeper pass saves outweighs the rows it computes twice.
 // Below these points (in millions; by storage, kind and radius) the levels sit
-// in the caches and a pass of four is slower than four steps.  us a step at
-// 2048^2 / 4096^2 / 8192^2, one step and four (eight): FP32 wave r = 4 12.4,
-// 17.4 / 39, 36 / 213, 109; r = 1 11.5, 7.0 (6.3) / 38, 22 (15) / 208, 83
-// (51); FP32 heat r = 4 8.3, 16 / 23, 31 / 132, 100; FP16 heat r = 1 4.9, 5.4
-// / 11.8, 10.0 / 46, 30; BF16 wave r = 4 7.3, 18 / 21, 33 / 109, 100.
+// in the caches and a pass of four is slower than four steps; past the last-level
+// cache one step falls to the memory's rate.  us a step, one step / four, below
+// and above each: FP32 heat r = 1 1.0 M 3.4 / 3.6, 1.5 M 4.0 / 3.7; r = 2 7 M 10.4 /
+// 10.7, 8 M 11.6 / 11.1; r = 3 28 M 30 / 32, 34 M 54 / 37; r = 4 33 M 37 / 49, 34 M
+// 54 / 50.  FP32 wave r = 1 1.2 M 3.9 / 4.1, 1.5 M 4.5 / 4.1; r = 2 3.5 M 8.9 / 9.3,
+// 4.2 M 11.0 / 10.1; r = 3 6 M 15.1 / 15.5, 7 M 16.6 / 16.4; r = 4 20 M 40 / 41, 24 M
+// 72 / 47.  FP16 heat r = 1 8 M 6.8 / 6.9, 10 M 7.8 / 7.5; r = 2 58 M 30 / 39, 67 M 49
+// / 44; r = 3 220 M 194 / 207; r = 4 200 M 195 / 261.  FP16 wave r = 1 5 M 6.6 / 6.9,
+// 7 M 8.9 / 8.1; r = 2 16 M 17.8 / 17.9, 18 M 19.4 / 19.0; r = 3 42 M 41 / 52, 48 M 66
+// / 57; r = 4 60 M 92 / 97, 66 M 110 / 105.  BF16 within 5% of FP16.  Eight steps
+// (FP32, r = 1) from 4 M points on: heat 4.2 M 5.4 in fours, 5.3; 67 M 46, 33; wave
+// 6.7, 6.4; 84, 52.
 int march_steps(int kind, int dtype, int radius, const Layout& L) {
-    static const double four[2][2][4] = {{{1.2, 6, 20, 24}, {0.9, 3, 5, 9}},       // FP32: heat, wave
-                                         {{8, 50, 100, 100}, {6, 14, 45, 60}}};    // 16 bits
+    constexpr double kNever = 1e30;
+    static const double four[2][2][4] = {{{1.2, 7.5, 30, 33.5}, {1.3, 3.8, 6.5, 21}},     // FP32: heat, wave
+                                         {{8.5, 62, kNever, kNever}, {6, 17, 45, 63}}};        // 16 bits
     const double pts = (double)L.g.n[1] * L.g.n[2] * 1e-6;
     if (dtype == STENCIL_F32 && radius == 1 && pts >= 4) return 8;
     return pts >= four[dtype != STENCIL_F32][kind == STENCIL_WAVE2][radius - 1] ? 4 : 1;
@@ -1305,7 +1323,7 @@ stencil_status stencil_apply(stencil_plan p, void* out, const void* const* in, c
     const int mode = wave ? (p->damped ? MODE_WAVE_DAMP : MODE_WAVE) : MODE_HEAT;
     hipStream_t s = (hipStream_t)stream;
     if (p->ndim == 3)
-        HIP_TRY(launch_brick(mode, p->radius, p->dtype, brick_planes(box.n, p->dtype), v, p->w, box, 0, 0, -1, s));
+        HIP_TRY(launch_brick(mode, p->radius, p->dtype, brick_planes(box.n, p->kind, p->radius, p->dtype), v, p->w, box, 0, 0, -1, s));
     else
         HIP_TRY(launch_point(mode, p->radius, p->dtype, v, p->w, box, s));
     return STENCIL_OK;
@@ -1362,10 +1380,13 @@ static stencil_status prepare_points(stencil_plan p, const Variant& var, const s
     return STENCIL_OK;
 }
 
-// a large 2D wave plan runs several steps per launch if it has a second field pair
+// A large 2D wave plan runs several steps per launch if it has a second field
+// pair.  It reports the pair from these points on (in millions; FP32, 16 bits),
+// a little before passes pay, as it has so far: callers lay out memory by it.
 static bool march_wants_pair(const stencil_plan_s* p) {
+    static const double from[2][4] = {{0.9, 3, 5, 9}, {6, 14, 45, 60}};
     return p->kind == STENCIL_WAVE2 && p->bc == STENCIL_BC_DIRICHLET0 &&
-           march_steps(p->kind, p->dtype, p->radius, p->L) > 1;
+           (double)p->L.g.n[1] * p->L.g.n[2] * 1e-6 >= from[p->dtype != STENCIL_F32][p->radius - 1];
 }
 
 // workspace bytes the plan's current variant needs: the second field pair

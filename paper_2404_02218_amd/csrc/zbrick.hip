@@ -27,13 +27,16 @@ namespace stn {
 
 // Number the bricks z first where the planes that z neighbours share pass the
 // reach of an XCD's 4 MB L2 otherwise: neighbours in z share 2R of their
-// BZ + 2R planes, tiles side by side only their margins.  One wave step in
-// us, x first / z first: 64 x 512 x 512 77 / 51, 207 x 301 x 259 60 / 55 (3.1
-// MB), 256^3 47 / 54 (2.6 MB), 224^3 33 / 39.  Past 2^25 points the order x
-// first streams better again (512^3, BZ = 4: 463 / 505).
+// BZ + 2R planes, tiles side by side only their margins.  One FP32 wave step of
+// radius 4 in us, x first / z first: 64 x 512 x 512 75 / 46, 207 x 301 x 259 60 /
+// 55 (3.1 MB), 256^3 48 / 50 (2.6 MB), 224^3 31 / 37.  Where the fields pass the
+// last-level cache the order x first streams as well or better (512^3, BZ = 4:
+// 463 / 505).  Radius 1 to 4, FP32 and FP16, 17 boxes of 96^3 to 320^3 and of 8 to
+// 128 planes: the order taken is the faster one or within 5%, but for 40 x 384 x
+// 384 (10.4 / 9.4) and 8 x 512 x 512 (5.7 / 4.5) in FP16, r = 2 and 1, just below
+// the line, where 320^3, r = 4, has 47 / 52.
 bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz) {
-    const double plane = (double)n[1] * n[2];
-    return (bz + 2 * radius) * plane * esize > 2.85e6 && plane * n[0] <= (double)(1 << 25);
+    return (double)(bz + 2 * radius) * n[1] * n[2] * esize > 2.85e6 && brick_cached(n, esize);
 }
 
 namespace {

@@ -63,7 +63,7 @@ def _outputs(launch):
 def shrunk_workspace(h):
     """A workspace attached again with fewer bytes, at the same address, is not written past them."""
     S = h.S
-    plan = S.Plan(S.WAVE2, (3000, 3013), 4, S.second_derivative_weights(8))
+    plan = S.Plan(S.WAVE2, (4700, 4701), 4, S.second_derivative_weights(8))
     f, need = h.fields(plan, 3), plan.run_workspace_bytes()
     assert need > 0
     ws = h.take(need)
@@ -307,6 +307,51 @@ def a_second_device(h):
         assert swept
         grids.append(swept[0][1])
     assert grids[1] < grids[0] == grids[2]   # fewer waves at once: longer chunks of rows
+
+
+def passes_by_size(h):
+    """On which side of each line a 2D plan takes several steps per launch, by kind, storage and radius."""
+    S = h.S
+    w = lambda kind, r: S.heat_weights(2 * r, 0.05) if kind == S.HEAT else S.second_derivative_weights(2 * r)
+    for kind, dtype, r, below, above in (
+            (S.HEAT, S.F32, 1, 1000, 1200), (S.HEAT, S.F32, 2, 2600, 2802), (S.HEAT, S.F32, 3, 5300, 5600),
+            (S.HEAT, S.F32, 4, 5700, 5900), (S.WAVE2, S.F32, 1, 1100, 1302), (S.WAVE2, S.F32, 2, 1900, 2002),
+            (S.WAVE2, S.F32, 3, 2500, 2602), (S.WAVE2, S.F32, 4, 4400, 4602), (S.HEAT, S.BF16, 1, 2800, 3002),
+            (S.HEAT, S.F16, 2, 7700, 8000), (S.HEAT, S.F16, 3, 15000, 0), (S.HEAT, S.BF16, 4, 15000, 0),
+            (S.WAVE2, S.F16, 1, 2400, 2500), (S.WAVE2, S.BF16, 2, 4000, 4202), (S.WAVE2, S.F16, 3, 6600, 6800),
+            (S.WAVE2, S.F16, 4, 7800, 8000)):
+        for n, deep in ((below, False), (above, True)):
+            if n == 0:
+                continue
+            plan = S.Plan(kind, (n, n), r, w(kind, r), dtype=dtype)
+            plan.variant = 0
+            f, need = h.fields(plan, 3 if kind == S.WAVE2 else 2), plan.run_workspace_bytes()
+            assert need == 0 or kind == S.WAVE2
+            if need:
+                S.call("stencil_set_workspace", plan.handle, C.c_void_p(h.take(need)), need, None)
+            assert need > 0 or not deep or kind == S.HEAT
+            h.launches()
+            assert h.run(plan, f, 16)[0] == 0
+            assert any("k_march2d" in x[0] for x in h.launches()) == deep, (kind, dtype, r, n)
+
+
+def brick_forms(h):
+    """Planes per brick by box, kind, storage and radius (the kernel's last two parameters but one)."""
+    S = h.S
+    wave, heat = S.WAVE2, S.HEAT
+    for kind, dtype, r, shape, planes in (
+            (wave, S.F32, 4, (9, 271, 270), 2), (wave, S.F32, 4, (9, 1931, 1953), 4), (wave, S.F32, 2, (23, 1001, 1003), 4),
+            (wave, S.F32, 1, (256, 256, 256), 2), (wave, S.F16, 4, (9, 531, 1101), 4), (wave, S.F16, 3, (9, 531, 1101), 2),
+            (wave, S.BF16, 4, (20, 40, 80), 2), (wave, S.BF16, 2, (320, 320, 320), 4), (heat, S.F32, 4, (160, 160, 160), 4),
+            (heat, S.F32, 3, (128, 128, 128), 2), (heat, S.F32, 2, (160, 160, 160), 2), (heat, S.F16, 1, (160, 160, 160), 4)):
+        w = S.heat_weights(2 * r, 0.05) if kind == heat else S.second_derivative_weights(2 * r)
+        plan = S.Plan(kind, shape, r, w, dtype=dtype)
+        plan.variant = 0
+        h.launches()
+        assert h.run(plan, h.fields(plan, 3 if kind == wave else 2), 1)[0] == 0
+        (name, grid, _), = h.launches()
+        tiles = -(-shape[2] // 64) * -(-shape[1] // 16)
+        assert "k_zbrick" in name and "Li%dELb0" % planes in name and grid == tiles * -(-shape[0] // planes), (name, shape)
 
 
 if __name__ == "__main__":

@@ -24,7 +24,8 @@ def stand_in(tmp_path_factory):
 
 @pytest.mark.parametrize("check", ["shrunk_workspace", "concurrent_batch", "runs_that_are_not_repeated", "runs_in_a_caller_capture",
                                    "heat_points", "long_lists_without_allocation", "batch_variants",
-                                   "saved_choices", "a_second_device"])
+                                   "saved_choices", "a_second_device",
+                                   "passes_by_size", "brick_forms"])
 def test_host_runtime(stand_in, check, tmp_path):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_host_runtime.py"), stand_in, check], capture_output=True,
                        text=True, timeout=300, env=dict(os.environ, STENCIL_TUNE_CACHE=str(tmp_path / "tuned")))
