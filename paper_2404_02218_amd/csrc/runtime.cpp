@@ -3474,7 +3474,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             v.g = L.g;
             Variant vs = var;
             vs.zc = zcs[i];
-            if (var.zmarch || var.tb) set_tiling(v, L, vs);
+            set_tiling(v, L, vs);
             views.push_back(v);
             bst.push_back(bst.back() + (int)zmarch_blocks(v));
         }
@@ -3559,13 +3559,7 @@ stencil_status stencil_tune(stencil_plan p, void* const* fields, int reps, void*
             if (p->batch)
                 return launch_zmarch_batch(p->radius, p->dtype, var.cfg, (const ZView*)vt.buf.p, (const int*)bs.buf.p,
                                            bst.back(), p->w, 0, 0, -1, s);
-            if (var.zmarch) return launch_zmarch(mode, p->radius, p->dtype, var.cfg, views[0], p->w, 0, 0, -1, s);
-            Box3 box{};
-            for (int a = 0; a < 3; a++) {
-                box.lo[a] = 0;
-                box.n[a] = p->L.g.n[a];
-            }
-            return launch_point(mode, p->radius, p->dtype, views[0], p->w, box, s);
+            return launch_zmarch(mode, p->radius, p->dtype, var.cfg, views[0], p->w, 0, 0, -1, s);
         };
         // a variant the runtime refuses to launch (e.g. more LDS than this
         // device allows) is skipped; any other error ends tuning
