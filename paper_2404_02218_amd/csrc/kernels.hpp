@@ -249,8 +249,9 @@ inline bool brick_cached(const int64_t* n, size_t esize) {
 // whether the bricks of a box of n points run z first
 bool brick_zfast(const int64_t* n, int radius, size_t esize, int bz);
 // batched shots in bricks of kBatchBrick planes; d_block_map: (shot, tile x, tile
-// y, z-chunk) of every workgroup, tile x -1 for the one that records the
-// shot's receivers, shot -1 for padding
+// y, z-chunk) of every workgroup, shot -1 for padding (a shot's receivers are
+// recorded by the workgroup of its first brick); long_lists: a shot's tile has
+// more than 64 sources
 inline constexpr int kBatchBrick = 2;
 hipError_t launch_brick_batch(int radius, int dtype, const ZView* d_views, const int* d_block_map, int nblocks,
                               bool long_lists, const Coefs& w, int parity, int arow, int trow, hipStream_t s);

@@ -25,12 +25,11 @@
 // for bit.
 //
 // One thread per point with its taps from the caches, a launch each for the
-// sources and the receivers, was bound by 4r + 1 scalar loads a point on large
-// grids and by the launches on small ones.  us a step before / now: FP32 wave
-// r = 4, 8192^2 326 / 110 (T = 4: 95 VALU instructions per 4 points and step,
-// issued 54% of the time at two waves per SIMD, 3.6 TB/s), 2048^2 23 / 12,
-// 256^2 6.6 / 3.8; r = 1, 8192^2 265 / 51 (T = 8); FP32 heat r = 1, 8192^2
-// 230 / 33.
+// sources and the receivers, was bound by 4r + 1 scalar loads a point.  us a
+// step before / now: FP32 wave r = 4, 8192^2 326 / 110 (T = 4: 95 VALU
+// instructions per 4 points and step, issued 54% of the time at two waves per
+// SIMD, 3.6 TB/s); r = 1, 8192^2 265 / 51 (T = 8); FP32 heat r = 1, 8192^2 230 /
+// 33.
 #include <algorithm>
 
 #include "strip2d.hpp"

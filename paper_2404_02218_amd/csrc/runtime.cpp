@@ -206,7 +206,7 @@ Variant variant_of(int v) {
 
 // Default variant: the brick kernel (variant 0) up to 12M points, where the
 // z-march leaves compute units idle (one FP32 wave step, brick / the best
-// z-march: 128^3 7.9 / 24 us, 192^3 21 / 26, 224^3 33 / -, 256^3 47 / 44).
+// z-march: 128^3 7.0 / 24 us, 192^3 19 / 26, 224^3 31 / -, 256^3 47 / 44).
 // Past that the first z-marching tile shape, with the longest z-chunk that
 // still gives at least 4 workgroups per compute unit (256 CUs).
 int default_variant(const Layout& L) {
@@ -310,7 +310,9 @@ struct stencil_plan_s {
     // batch
     std::vector<Layout> shots;
     std::vector<PointTables> shot_src, shot_rec;
-    DevTable views, block_map;   // block_map: (shot, block within the shot) per workgroup
+    // block_map, per workgroup: (shot, block within the shot), in bricks (shot,
+    // tile x, tile y, z-chunk)
+    DevTable views, block_map;
     std::vector<int> bstart;
     int nblocks = 0;             // workgroups of a batched launch (with padding)
     std::vector<int> group_first;   // in bricks: the workgroups of each group of shots

@@ -1,9 +1,10 @@
 // The 3D sweep of a box by bricks (k_zbrick): a workgroup
-// computes a brick of 64 x 16 x BZ points.  Every load of the brick (the
-// threads' own z columns, the in-plane margins, u_prev and beta) is issued
-// before the first one is used and a single barrier separates them from the
-// arithmetic, so a workgroup pays the memory latency once, where the
-// z-marching kernel pays it again on every plane of its chunk.
+// computes a brick of 64 x 16 x BZ points.  The loads of the brick (the
+// threads' own z columns, the in-plane margins, u_prev and beta) come before the
+// arithmetic, a single barrier between them, so a workgroup pays the memory
+// latency once or twice (the compiler copies a group of the FP32 column's loads
+// while the others are under way, and waits for it), where the z-marching
+// kernel pays it again on every plane of its chunk.
 //
 // It serves what the z-march leaves idle: grids with too few xy tiles and
 // z-chunks to fill 256 compute units, and boxes (stencil_apply on the boundary
@@ -14,9 +15,9 @@
 //
 // One FP32 wave step, radius 4, in us (this kernel / best z-march / one
 // thread per point with its taps from the caches, which this replaces):
-// 64^3 4.0 / 23 / -, 61 x 75 x 90 4.9 / 23 / 6.3 plus 3.9 of injection and
-// recording, 128^3 7.9 / 24 / 14, 192^3 21 / 26, 256^3 47 / 44, 512^3 463 /
-// 372.  FP16 207 x 301 x 259: 31 / 35.
+// 64^3 3.7 / 23 / -, 61 x 75 x 90 with a source and 16 receivers 4.7 / 23 / 6.3
+// plus 3.9 of injection and recording, 128^3 7.0 / 24 / 14, 192^3 19 / 26, 256^3
+// 47 / 44, 512^3 463 / 372.  FP16 207 x 301 x 259: 31 / 35.
 //
 // Each point takes the canonical operation order (device.hpp), so the results
 // are those of every other sweep kernel bit for bit.
