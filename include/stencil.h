@@ -168,9 +168,10 @@ stencil_status stencil_apply(stencil_plan plan, void* out, const void* const* in
  * src/rec may be NULL.  The multi-step heat variants serve runs without them;
  * a heat run with sources or receivers takes plain sweeps (the same bits).
  * The launches of a run of two or more steps are
- * captured into one HIP graph per (pointers, nsteps, variant, tables) at the
- * second call in a row, and replayed from then on (on a stream that the caller
- * is capturing they go into that capture); with the environment variable STENCIL_NO_GRAPH set to a value
+ * captured into one HIP graph per (pointers, nsteps, variant, tables), behind
+ * the first call or (small grids) at the second one in a row, and replayed
+ * from then on (on a stream that the caller is capturing they go into that
+ * capture); with the environment variable STENCIL_NO_GRAPH set to a value
  * other than 0 they are enqueued directly instead (the same kernels and
  * bits).  The temporally blocked wave variants need a caller workspace
  * (stencil_run_workspace / stencil_set_workspace); without one the call

@@ -307,6 +307,7 @@ struct stencil_plan_s {
     hipGraphExec_t gexec = nullptr;
     std::vector<int64_t> gkey;   // of the last run of two or more steps, and of gexec
     bool glaunched = false;      // gexec has been launched
+    bool gwasted = false;        // the last graph was not: the next one waits for a second call
     // batch
     std::vector<Layout> shots;
     std::vector<PointTables> shot_src, shot_rec;
@@ -1478,13 +1479,16 @@ constexpr int64_t kCaptureBehind = int64_t(1) << 22;
 // from a captured graph where calls with the same key follow each other.
 // Capturing and instantiating a graph takes the host longer than launching its
 // kernels, with the device idle, and is lost on a run that is not repeated, as
-// where an odd step count makes the fields change places from call to call.  So
-// the second call in a row captures: behind its own launches for sweeps of
-// kCaptureBehind points, which keep the device busy meanwhile, and before them
-// for smaller ones.  A plan's first run, captured in front / direct: 100 heat
+// where an odd step count makes the fields change places from call to call.
+// Sweeps of kCaptureBehind points keep the device busy longer than that: their
+// graph is captured behind the first, direct run, in its shadow, unless the plan's
+// last graph was never launched.  Then, and for smaller sweeps, the second call
+// in a row captures.  A plan's first run, captured in front / direct: 100 heat
 // steps of 256^2 222 / 139 us (replayed 57), 200 wave steps of 61 x 75 x 90
 // 1686 / 1176 (980), 24 of 207 x 301 x 259 in FP16 1083 / 934 (773), 32 of
-// 8192^2 4119 / 4034 (3710).
+// 8192^2 4119 / 4034 (3710).  Not all of a large graph hides behind the run: 400
+// wave steps of 512^3 in 200 launches take 118 ms directly, 125 with the capture
+// behind them, 116 replayed.
 //
 // On a stream that the caller is capturing, the launches go into that capture
 // and the plan's own graph stays as it is.
@@ -1501,20 +1505,20 @@ static stencil_status replay(stencil_plan p, const std::vector<int64_t>& key,
     hipStreamCaptureStatus on = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &on) != hipSuccess) (void)hipGetLastError();
     if (on != hipStreamCaptureStatusNone) return enqueue(s);
-    if (key != p->gkey) {
-        if (p->gexec) {
-            if (p->glaunched) HIP_TRY(hipStreamSynchronize(s));
-            HIP_TRY(hipGraphExecDestroy(p->gexec));
-            p->gexec = nullptr;
-        }
-        p->gkey = key;
-        return enqueue(s);
+    const bool behind = !once && run_points(p) >= kCaptureBehind, again = key == p->gkey;
+    if (!again && p->gexec) {
+        if (p->glaunched) HIP_TRY(hipStreamSynchronize(s));
+        p->gwasted = !p->glaunched;
+        HIP_TRY(hipGraphExecDestroy(p->gexec));
+        p->gexec = nullptr;
     }
+    p->gkey = key;
     if (!p->gexec) {
-        if (once && p->branch_captured) return enqueue(s);
+        const bool capture = again ? !once || !p->branch_captured : behind && !p->gwasted;
+        if (!capture) return enqueue(s);
         p->branch_captured |= once;
         p->glaunched = false;
-        if (run_points(p) >= kCaptureBehind && !once) {
+        if (behind) {
             ST_TRY(enqueue(s));
             // the run is on its way: without its graph the next one goes as this one did
             if (capture_run(p, enqueue) != STENCIL_OK) {
